@@ -20,7 +20,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpolyspec.so")
 SOURCES = ["fft.hip", "contract_tiles_lo.hip", "contract_tiles_hi.hip", "contract_j3.hip", "reduce.hip",
-           "adjoint.hip", "adjoint_fp32.hip", "adjoint_bf16.hip", "adjoint_fp16.hip", "util.hip", "plan.cpp"]
+           "adjoint.hip", "adjoint_sym_fp32.hip", "adjoint_sym_bf16.hip", "adjoint4_sym_fp32.hip",
+           "adjoint4_sym_bf16.hip", "adjoint_fp16.hip", "adjoint4_fp16.hip", "util.hip", "plan.cpp"]
 ARCH = "gfx950"
 ROCM_LLVM = "/opt/rocm/llvm/bin"
 PACKED_F32 = re.compile(r"\bv_pk_(add|mul|fma)_f32\b")

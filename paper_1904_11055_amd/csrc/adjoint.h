@@ -1,4 +1,6 @@
-// Adjoint product of the estimator (not in the paper: the gradient extension).
+// Adjoint product of the estimator (not in the paper: the gradient extension): what the
+// forms of the adjoint share, and the kernels of the FP16 split.  FP32 and SPLIT_BF16 take
+// the symmetric form of adjoint_sym.h.
 //
 // Order 3: a_m[x] = sum_{u <= v} W[m][(u, v)] d_u[x] d_v[x] with
 // W[m][(u, v)] = (times m occurs in t) dL/dB_t f / (N^3 n_t), t = sort(m, u, v),
@@ -6,21 +8,14 @@
 // fields, once per position of m in t).
 // Order 4: a_m[x] = sum_{u <= v <= w} W4[m][(u, v, w)] d_u[x] d_v[x] d_w[x], likewise.
 //
-// Both are one matrix product per workgroup: rows m (32 per block), columns the grid
-// points, and the reduction over the row products of the other fields.  A reduction
-// step is a 16-shell chunk uc of u with the rest fixed (v, or the item (v, w)): the
-// B operand is the 16 fields d_u at the wave's 32 points times the scalar field
-// d_v (d_v d_w) at each point, formed on the VALU from fields held in registers, and
-// the A operand is the matching weight block from LDS.  The products go straight
-// into the output accumulators, so nothing on the VALU waits for a matrix result.
+// Rows m, columns the grid points; a reduction step is a 16-shell chunk uc of u with the
+// rest fixed (v, or the item (v, w)): Y = W_v d_u on the matrix cores with the
+// register-held fields as B operand and a weight block from LDS as A, then
+// a_m += d_v Y (d_v d_w Y).
 //
-// Precisions: FP32 (v_mfma_f32_32x32x2_f32 on the float32 products), SPLIT_BF16
-// (products formed in float32, split hi + lo, hh + hl + lh with
-// v_mfma_f32_32x32x16_bf16), SPLIT_FP16 (v_mfma_f32_32x32x16_f16; the fields carry
-// the forward's per-shell power-of-two scale and the pair products are formed from
-// their split halves with error-free half-precision products; each weight row m
-// carries its own power of two so that its largest magnitude lies in [2^14, 2^15),
-// and the epilogue removes it exactly).
+// SPLIT_FP16 (v_mfma_f32_32x32x16_f16, hh + hl + lh): the fields carry the forward's
+// per-shell power-of-two scale; each weight row m carries its own power of two so that
+// its largest magnitude lies in [2^14, 2^15), and the epilogue removes it exactly.
 #pragma once
 
 #include "fft_core.h"
@@ -48,16 +43,18 @@ __device__ __forceinline__ int adj_row_exp(const unsigned long long* rowmax, int
   return kAdjRowTop - ilogb(m);
 }
 
-template <int NF>
-constexpr int adj_pencils() { return NF ? 32 * (kAdjPts / NF) : 0; }
-template <int NF>
+// Row transform of the epilogue: 8 KB pencils (two rows m each) for every x2-row of the
+// workgroup, KB 16-shell blocks of m.
+template <int NF, int KB>
+constexpr int adj_pencils() { return NF ? 8 * KB * (kAdjPts / NF) : 0; }
+template <int NF, int KB>
 constexpr size_t adj_fft_lds_bytes() {
-  return NF ? ((size_t)adj_pencils<NF>() * pencil_stride<NF>() + stage_tw_size<NF>()) * sizeof(cplx<float>) : 0;
+  return NF ? ((size_t)adj_pencils<NF, KB>() * pencil_stride<NF>() + stage_tw_size<NF>()) * sizeof(cplx<float>) : 0;
 }
-template <int NF>
+template <int NF, int KB>
 constexpr size_t adj_lds_bytes() {
   const size_t stage = (size_t)2 * kAdjStageWords * sizeof(uint4);
-  return adj_fft_lds_bytes<NF>() > stage ? adj_fft_lds_bytes<NF>() : stage;
+  return adj_fft_lds_bytes<NF, KB>() > stage ? adj_fft_lds_bytes<NF, KB>() : stage;
 }
 // Order 4 with NC chunks of 16 shells (2: up to 32 shells, one 32-row block of m; 4: up
 // to 64, two blocks): items (w, v) per LDS stage, operand words per stage and per thread.
@@ -73,35 +70,32 @@ static_assert(adj4_piece<2>() * kAdjThreads == adj4_stage_words<2>() &&
 template <int NF, int NC>
 constexpr size_t adj4_lds_bytes() {
   const size_t stage = (size_t)2 * adj4_stage_words<NC>() * sizeof(uint4);   // double buffered
-  return adj_fft_lds_bytes<NF>() > stage ? adj_fft_lds_bytes<NF>() : stage;
+  return adj_fft_lds_bytes<NF, NC>() > stage ? adj_fft_lds_bytes<NF, NC>() : stage;
 }
 
-// Writes the accumulated adjoint fields: acc[pb][mb] of lane l, register i is row
-// m = 32 mb + 8 (i / 4) + 4 (l / 32) + i % 4 at point l % 32 of column block pb.
+// Writes the accumulated adjoint fields: the lane's value j (j < 8 KB) of column block pb
+// is val(pb, j), row m = row(j) at point col of the block (KB 16-shell blocks of m).
 // Fused form (NF = N <= 512): the workgroup's 512 points are 512 / N whole rows of x2,
 // so the rows are transformed to the half spectrum q2 = 0..Kc right here (two rows m
 // per complex FFT, the same real-to-complex pass as the backward's first transform)
 // and written to H2; the fields never reach HBM.  NF = 0 writes a_m to A.
-template <int NF>
-__device__ __forceinline__ void adjoint_epilogue(const f32x16 (&acc)[kAdjPB][kAdjMaxMb], unsigned char* lds, int lane,
-                                                 int wave, int hh, int col, int b, long long xw, int n_shells,
-                                                 long long G, float* __restrict__ A, cplx<float>* __restrict__ H2,
-                                                 const cplx<float>* __restrict__ tw, const Geom& g) {
+template <int NF, int KB, typename Val, typename Row>
+__device__ __forceinline__ void adjoint_epilogue(Val&& val, Row&& row, unsigned char* lds, int wave, int col, int b,
+                                                 long long xw, int n_shells, long long G, float* __restrict__ A,
+                                                 cplx<float>* __restrict__ H2, const cplx<float>* __restrict__ tw,
+                                                 const Geom& g) {
   if constexpr (NF == 0) {
     float* Ab = A + (size_t)b * n_shells * G + xw;
 #pragma unroll
     for (int pb = 0; pb < kAdjPB; ++pb) {
 #pragma unroll
-      for (int mb = 0; mb < kAdjMaxMb; ++mb) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int m = mb * 32 + 8 * (i / 4) + 4 * hh + (i % 4);
-          if (m < n_shells) Ab[(size_t)m * G + 32 * pb] = acc[pb][mb][i];
-        }
+      for (int j = 0; j < 8 * KB; ++j) {
+        const int m = row(j);
+        if (m < n_shells) Ab[(size_t)m * G + 32 * pb] = val(pb, j);
       }
     }
   } else {
-    constexpr int P = adj_pencils<NF>();          // pencil rho * 32 + m / 2 holds rows m, m + 1 of x2-row rho
+    constexpr int P = adj_pencils<NF, KB>();      // pencil rho * 8 KB + m / 2 holds rows m, m + 1 of x2-row rho
     constexpr int NS = pencil_stride<NF>();
     cplx<float>* buf = reinterpret_cast<cplx<float>*>(lds);
     cplx<float>* stw = buf + P * NS;
@@ -111,14 +105,8 @@ __device__ __forceinline__ void adjoint_epilogue(const f32x16 (&acc)[kAdjPB][kAd
       const int x = wave * 32 * kAdjPB + 32 * pb + col;   // point within the workgroup
       const int rho = x / NF, x2 = x % NF;
 #pragma unroll
-      for (int mb = 0; mb < kAdjMaxMb; ++mb) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int m = mb * 32 + 8 * (i / 4) + 4 * hh + (i % 4);
-          float* slot = reinterpret_cast<float*>(&buf[(rho * 32 + (m >> 1)) * NS + pad8(x2)]);
-          slot[m & 1] = acc[pb][mb][i];
-        }
-      }
+      for (int j = 0; j < 8 * KB; j += 2)   // rows j, j + 1 are m, m + 1 with m even
+        buf[(rho * 8 * KB + (row(j) >> 1)) * NS + pad8(x2)] = cplx<float>{val(pb, j), val(pb, j + 1)};
     }
     build_stage_twiddles<float, NF, kAdjThreads>(stw, tw);
     __syncthreads();
@@ -128,7 +116,7 @@ __device__ __forceinline__ void adjoint_epilogue(const f32x16 (&acc)[kAdjPB][kAd
     for (int u = threadIdx.x; u < 2 * P * g.B2; u += kAdjThreads) {
       const int r = u / g.B2, c = u % g.B2;
       const int pen = r >> 1;
-      const int m = 2 * (pen & 31) + (r & 1), rho = pen >> 5;
+      const int m = 2 * (pen % (8 * KB)) + (r & 1), rho = pen / (8 * KB);
       if (m >= n_shells) continue;
       const cplx<float> Zp = buf[pen * NS + pad8(c)];
       const cplx<float> Zm = buf[pen * NS + pad8((NF - c) & (NF - 1))];
@@ -201,45 +189,6 @@ __device__ __forceinline__ unsigned adj_scalar(const AdjFields<PREC, NC>& f, int
   return VV / 8 == 0 ? sw[0] : sw[1];
 }
 
-// B operand: fields of chunk uc at this lane's points times the scalar s (bits from
-// adj_scalar, or an FP16 split pair already scaled).
-template <int PREC, int NC>
-__device__ __forceinline__ Operand<PREC> adj_pair_operand(const AdjFields<PREC, NC>& f, int pb, int uc, unsigned s) {
-  if constexpr (PREC == kFP16) {
-    Operand<kFP16> sv;
-    const _Float16 sh = __builtin_bit_cast(_Float16, (unsigned short)(s & 0xffffu));
-    const _Float16 sl = __builtin_bit_cast(_Float16, (unsigned short)(s >> 16));
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      sv.hi[r] = sh;
-      sv.lo[r] = sl;
-    }
-    return pair_f16(f.H[pb][uc], sv);
-  } else {
-    const float sf = __uint_as_float(s);
-    float x[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = f.F[pb][uc][r] * sf;
-    return make_operand<PREC>(x, 1.f);
-  }
-}
-
-// Product of two scalar fields as an FP16 split pair (error-free product of the split
-// halves) times 2^-shift, packed like adj_scalar's words.
-__device__ __forceinline__ unsigned f16_scalar_product(unsigned a, unsigned b, int shift) {
-  const _Float16 ah = __builtin_bit_cast(_Float16, (unsigned short)(a & 0xffffu));
-  const _Float16 al = __builtin_bit_cast(_Float16, (unsigned short)(a >> 16));
-  const _Float16 bh = __builtin_bit_cast(_Float16, (unsigned short)(b & 0xffffu));
-  const _Float16 bl = __builtin_bit_cast(_Float16, (unsigned short)(b >> 16));
-  const _Float16 sc = (_Float16)ldexpf(1.0f, -shift);
-  _Float16 ph = ah * bh;
-  const _Float16 e = __builtin_fmaf16(ah, bh, -ph);
-  _Float16 pl = __builtin_fmaf16(ah, bl, __builtin_fmaf16(al, bh, e));
-  ph = ph * sc;   // a power of two: exact while in the normal range
-  pl = pl * sc;
-  return (unsigned)__builtin_bit_cast(unsigned short, ph) | ((unsigned)__builtin_bit_cast(unsigned short, pl) << 16);
-}
-
 template <int PREC>
 __device__ __forceinline__ void adj_mma(f32x16& acc, const Operand<PREC>& a, const Operand<PREC>& b) {
   if constexpr (PREC == kFP16) {
@@ -282,36 +231,9 @@ __device__ __forceinline__ void adj_unscale(f32x16 (&acc)[kAdjPB][kAdjMaxMb], co
   }
 }
 
-// One partner v of the order-3 adjoint: Y[mb] = sum over the chunks uc <= VC of the
-// weight block (uc, mb) times the field operands, for the first NM m-blocks, then
-// a_m += d_v Y[mb].  Straight-line code, so that the multiply-adds of one m-block are
-// scheduled under the products of the next.
-template <int PREC, int NM, int VC>
-__device__ __forceinline__ void adj_partner(f32x16 (&acc)[kAdjPB][kAdjMaxMb], const float (&dv)[kAdjPB],
-                                            const uint4* wv, const Operand<PREC> (&fop)[kAdjPB][4], int lane) {
-  f32x16 Y[NM][kAdjPB];
-  static_for<NM>([&](auto mbc) {
-    constexpr int mb = decltype(mbc)::value;
-    static_for<VC + 1>([&](auto ucc) {
-      constexpr int uc = decltype(ucc)::value;
-      const uint4* blk = wv + (uc * kAdjMaxMb + mb) * 2 * 64;
-      const Operand<PREC> Wop = op_from_words<PREC>(blk[lane], blk[64 + lane]);
-#pragma unroll
-      for (int pb = 0; pb < kAdjPB; ++pb) {
-        if constexpr (uc == 0) adj_mma_first<PREC>(Y[mb][pb], Wop, fop[pb][uc]);
-        else adj_mma<PREC>(Y[mb][pb], Wop, fop[pb][uc]);
-      }
-    });
-  });
-#pragma unroll
-  for (int mb = 0; mb < NM; ++mb)
-#pragma unroll
-    for (int pb = 0; pb < kAdjPB; ++pb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[pb][mb][i] = fmaf(dv[pb], Y[mb][pb][i], acc[pb][mb][i]);
-}
-
-// Order 3.  A workgroup of 8 waves owns 512 grid points (each wave two 32-point
+// Order 3, FP16 split (the other precisions: adjoint_sym.h; here every weight row of an m
+// carries a power of two of its own, which the symmetric form has no place for).  A
+// workgroup of 8 waves owns 512 grid points (each wave two 32-point
 // column blocks) and every m.  For each partner v and 32-row block mb of m,
 // Y = sum over the chunks uc <= v / 16 of W_v[uc, mb] d_u runs on the matrix cores with
 // the register-held field operands as B, and a_m += d_v Y is one float32 multiply-add
@@ -322,7 +244,7 @@ __device__ __forceinline__ void adj_partner(f32x16 (&acc)[kAdjPB][kAdjMaxMb], co
 // block read from LDS feeds both column blocks.  Values of v, and (v, mb) blocks,
 // without any weight (vmask: bit 2 uc + mb) are skipped.
 // MBN: 32-row blocks of m that can hold a weight (1 when n_shells <= 32, else 2).
-template <int PREC, int NF, int MBN>
+template <int NF, int MBN>
 __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __restrict__ D,
                                                              const uint4* __restrict__ W,
                                                              const int* __restrict__ vmask,
@@ -331,7 +253,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __re
                                                              int n_shells, long long G, float* __restrict__ A,
                                                              cplx<float>* __restrict__ H2,
                                                              const cplx<float>* __restrict__ tw, Geom g) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[adj_lds_bytes<NF>()];
+  __shared__ __attribute__((aligned(16))) unsigned char lds[adj_lds_bytes<NF, 2 * MBN>()];
   auto wst = reinterpret_cast<uint4(*)[kAdjStageWords]>(lds);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -341,18 +263,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __re
   const long long xw = (long long)blockIdx.x * kAdjPts + wave * 32 * kAdjPB + col;
   const float* Db = D + (size_t)b * n_shells * G;
 
-  AdjFields<PREC, 4> f;
-  adj_load_fields<PREC, 4>(f, Db, G, xw, hh, n_shells, absmax, b);
-  // the fields as B operands (FP16: the split operands themselves)
-  Operand<PREC> fop[kAdjPB][4];
-#pragma unroll
-  for (int pb = 0; pb < kAdjPB; ++pb)
-#pragma unroll
-    for (int uc = 0; uc < 4; ++uc) {
-      if constexpr (PREC == kFP16) fop[pb][uc] = f.H[pb][uc];
-      else fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
-    }
-
+  AdjFields<kFP16, 4> f;
+  adj_load_fields<kFP16, 4>(f, Db, G, xw, hh, n_shells, absmax, b);
   // the weight-block masks of every v, one per lane (bit 2 uc + mb)
   const int vml = lane < n_shells ? vmask[lane] : 0;
 
@@ -405,49 +317,41 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __re
       const int mask = __builtin_amdgcn_readlane(vml, v);
       if (mask != 0) {
         const uint4* wv = wst[st & 1] + vi * kAdjWPerV;
-        // d_v at the lane's points as float32 (FP16: the scaled value)
+        // d_v at the lane's points as float32 (the scaled value)
         float dv[kAdjPB];
 #pragma unroll
         for (int pb = 0; pb < kAdjPB; ++pb) {
-          const unsigned w = adj_scalar<PREC, 4, vc, vv>(f, pb);
-          if constexpr (PREC == kFP16)
-            dv[pb] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w & 0xffffu)) +
-                     (float)__builtin_bit_cast(_Float16, (unsigned short)(w >> 16));
-          else
-            dv[pb] = __uint_as_float(w);
+          const unsigned w = adj_scalar<kFP16, 4, vc, vv>(f, pb);
+          dv[pb] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w & 0xffffu)) +
+                   (float)__builtin_bit_cast(_Float16, (unsigned short)(w >> 16));
         }
-        if constexpr (PREC != kFP16 && vc > 0) {
-          adj_partner<PREC, MBN, vc>(acc, dv, wv, fop, lane);   // every block, straight-line
-        } else {
-          // blocks (uc, mb) without a weight skipped (v < 16: one chunk, and m-block 1
-          // rarely holds a weight; FP16: the straight-line form spills registers)
+        // blocks (uc, mb) without a weight skipped (the straight-line form spills registers)
 #pragma unroll
-          for (int mb = 0; mb < MBN; ++mb) {
-            if (!(mask & (0x55 << mb))) continue;   // no weight in this block of m
-            f32x16 Y[kAdjPB];
-            static_for<vc + 1>([&](auto ucc) {
-              constexpr int uc = decltype(ucc)::value;
-              const bool on = (mask >> (2 * uc + mb)) & 1;   // a weight in block (uc, mb)
-              if (on) {
-                const uint4* blk = wv + (uc * kAdjMaxMb + mb) * 2 * 64;
-                const Operand<PREC> Wop = op_from_words<PREC>(blk[lane], blk[64 + lane]);
+        for (int mb = 0; mb < MBN; ++mb) {
+          if (!(mask & (0x55 << mb))) continue;   // no weight in this block of m
+          f32x16 Y[kAdjPB];
+          static_for<vc + 1>([&](auto ucc) {
+            constexpr int uc = decltype(ucc)::value;
+            const bool on = (mask >> (2 * uc + mb)) & 1;   // a weight in block (uc, mb)
+            if (on) {
+              const uint4* blk = wv + (uc * kAdjMaxMb + mb) * 2 * 64;
+              const Operand<kFP16> Wop = op_from_words<kFP16>(blk[lane], blk[64 + lane]);
 #pragma unroll
-                for (int pb = 0; pb < kAdjPB; ++pb) {
-                  if constexpr (uc == 0) adj_mma_first<PREC>(Y[pb], Wop, fop[pb][uc]);
-                  else adj_mma<PREC>(Y[pb], Wop, fop[pb][uc]);
-                }
-              } else if constexpr (uc == 0) {
-#pragma unroll
-                for (int pb = 0; pb < kAdjPB; ++pb)
-#pragma unroll
-                  for (int i = 0; i < 16; ++i) Y[pb][i] = 0.f;
+              for (int pb = 0; pb < kAdjPB; ++pb) {
+                if constexpr (uc == 0) adj_mma_first<kFP16>(Y[pb], Wop, f.H[pb][uc]);
+                else adj_mma<kFP16>(Y[pb], Wop, f.H[pb][uc]);
               }
-            });
+            } else if constexpr (uc == 0) {
 #pragma unroll
-            for (int pb = 0; pb < kAdjPB; ++pb)
+              for (int pb = 0; pb < kAdjPB; ++pb)
 #pragma unroll
-              for (int i = 0; i < 16; ++i) acc[pb][mb][i] = fmaf(dv[pb], Y[pb][i], acc[pb][mb][i]);
-          }
+                for (int i = 0; i < 16; ++i) Y[pb][i] = 0.f;
+            }
+          });
+#pragma unroll
+          for (int pb = 0; pb < kAdjPB; ++pb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[pb][mb][i] = fmaf(dv[pb], Y[pb][i], acc[pb][mb][i]);
         }
       }
       if (more && (vi == kAdjVG - 1)) {
@@ -456,11 +360,13 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __re
       }
     });
   });
-  adj_unscale<PREC>(acc, rowmax, b, hh);
-  adjoint_epilogue<NF>(acc, lds, lane, wave, hh, col, b, xw, n_shells, G, A, H2, tw, g);
+  adj_unscale<kFP16>(acc, rowmax, b, hh);
+  auto mfma_row = [&](int j) { return 32 * (j / 16) + 8 * (j % 16 / 4) + 4 * hh + j % 4; };
+  adjoint_epilogue<NF, 2 * MBN>([&](int pb, int j) { return acc[pb][j / 16][j % 16]; }, mfma_row, lds, wave, col, b, xw,
+                                n_shells, G, A, H2, tw, g);
 }
 
-// Order 4 (NC = 2: at most 32 shells, one 32-row block of m; NC = 4: at most 64 shells,
+// Order 4, FP16 split (NC = 2: at most 32 shells, one 32-row block of m; NC = 4: at most 64 shells,
 // two blocks).  Items (w, v <= w) in order of w; for each item and block of m,
 // Y = sum over the chunks uc <= v / 16 of W4_(v,w) d_u runs on the matrix
 // cores with the fields themselves as the B operand, and a_m += d_v d_w Y on the VALU,
@@ -471,7 +377,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __re
 // double buffered: the next stage is loaded into registers while one is in use, then
 // stored, with one barrier per stage.  d_w and the item masks of the next w are likewise
 // loaded a w ahead.
-template <int PREC, int NF, int NC>
+template <int NF, int NC>
 __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __restrict__ D,
                                                               const uint4* __restrict__ W,
                                                               const int* __restrict__ imask,
@@ -498,17 +404,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __r
   const uint4* Wb = W + (size_t)b * n_items * WPI;
   const int* Ib = imask;   // one mask per item, shared by the batch
 
-  AdjFields<PREC, NC> f;
-  adj_load_fields<PREC, NC>(f, Db, G, xw, hh, n_shells, absmax, b);
-  // the fields as B operands (FP16: the split operands themselves)
-  Operand<PREC> fop[kAdjPB][NC];
-#pragma unroll
-  for (int pb = 0; pb < kAdjPB; ++pb)
-#pragma unroll
-    for (int uc = 0; uc < NC; ++uc) {
-      if constexpr (PREC == kFP16) fop[pb][uc] = f.H[pb][uc];
-      else fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
-    }
+  AdjFields<kFP16, NC> f;
+  adj_load_fields<kFP16, NC>(f, Db, G, xw, hh, n_shells, absmax, b);
   f32x16 acc[kAdjPB][kAdjMaxMb];
 #pragma unroll
   for (int pb = 0; pb < kAdjPB; ++pb)
@@ -544,11 +441,10 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __r
 
   int buf = 0;
   for (int w = 0; w < n_shells; ++w) {
-    float dw[kAdjPB];   // FP16: d_w scaled like the register fields, times 2^-7
+    float dw[kAdjPB];   // d_w scaled like the register fields, times 2^-7
 #pragma unroll
     for (int pb = 0; pb < kAdjPB; ++pb) {
-      if constexpr (PREC == kFP16) dw[pb] = ldexpf(dw_next[pb], shell_scale_exp(absmax, b * n_shells + w) - kTripleShift);
-      else dw[pb] = dw_next[pb];
+      dw[pb] = ldexpf(dw_next[pb], shell_scale_exp(absmax, b * n_shells + w) - kTripleShift);
     }
     const int my_mask = mask_next;
     if (w + 1 < n_shells) {
@@ -580,22 +476,18 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __r
           f32x16 Y[kAdjPB];
           static_for<vc + 1>([&](auto ucc) {
             constexpr int uc = decltype(ucc)::value;   // no branch per chunk (zero weights where empty)
-            const Operand<PREC> Wop = op_from_words<PREC>(wv[uc * 128 + lane], wv[uc * 128 + 64 + lane]);
+            const Operand<kFP16> Wop = op_from_words<kFP16>(wv[uc * 128 + lane], wv[uc * 128 + 64 + lane]);
 #pragma unroll
             for (int pb = 0; pb < kAdjPB; ++pb) {
-              if constexpr (uc == 0) adj_mma_first<PREC>(Y[pb], Wop, fop[pb][uc]);
-              else adj_mma<PREC>(Y[pb], Wop, fop[pb][uc]);
+              if constexpr (uc == 0) adj_mma_first<kFP16>(Y[pb], Wop, f.H[pb][uc]);
+              else adj_mma<kFP16>(Y[pb], Wop, f.H[pb][uc]);
             }
           });
 #pragma unroll
           for (int pb = 0; pb < kAdjPB; ++pb) {
-            const unsigned dv = adj_scalar<PREC, NC, vc, vv>(f, pb);
-            float sv;
-            if constexpr (PREC == kFP16)
-              sv = (float)__builtin_bit_cast(_Float16, (unsigned short)(dv & 0xffffu)) +
-                   (float)__builtin_bit_cast(_Float16, (unsigned short)(dv >> 16));
-            else
-              sv = __uint_as_float(dv);
+            const unsigned dv = adj_scalar<kFP16, NC, vc, vv>(f, pb);
+            const float sv = (float)__builtin_bit_cast(_Float16, (unsigned short)(dv & 0xffffu)) +
+                             (float)__builtin_bit_cast(_Float16, (unsigned short)(dv >> 16));
             const float sc = sv * dw[pb];
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[pb][0][i] = fmaf(sc, Y[pb][i], acc[pb][0][i]);
@@ -604,13 +496,9 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __r
           float sc[kAdjPB];
 #pragma unroll
           for (int pb = 0; pb < kAdjPB; ++pb) {
-            const unsigned dv = adj_scalar<PREC, NC, vc, vv>(f, pb);
-            float sv;
-            if constexpr (PREC == kFP16)
-              sv = (float)__builtin_bit_cast(_Float16, (unsigned short)(dv & 0xffffu)) +
-                   (float)__builtin_bit_cast(_Float16, (unsigned short)(dv >> 16));
-            else
-              sv = __uint_as_float(dv);
+            const unsigned dv = adj_scalar<kFP16, NC, vc, vv>(f, pb);
+            const float sv = (float)__builtin_bit_cast(_Float16, (unsigned short)(dv & 0xffffu)) +
+                             (float)__builtin_bit_cast(_Float16, (unsigned short)(dv >> 16));
             sc[pb] = sv * dw[pb];
           }
 #pragma unroll
@@ -620,11 +508,11 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __r
             static_for<vc + 1>([&](auto ucc) {
               constexpr int uc = decltype(ucc)::value;
               const uint4* wb = wv + (uc * MB + mb) * 128;
-              const Operand<PREC> Wop = op_from_words<PREC>(wb[lane], wb[64 + lane]);
+              const Operand<kFP16> Wop = op_from_words<kFP16>(wb[lane], wb[64 + lane]);
 #pragma unroll
               for (int pb = 0; pb < kAdjPB; ++pb) {
-                if constexpr (uc == 0) adj_mma_first<PREC>(Y[pb], Wop, fop[pb][uc]);
-                else adj_mma<PREC>(Y[pb], Wop, fop[pb][uc]);
+                if constexpr (uc == 0) adj_mma_first<kFP16>(Y[pb], Wop, f.H[pb][uc]);
+                else adj_mma<kFP16>(Y[pb], Wop, f.H[pb][uc]);
               }
             });
 #pragma unroll
@@ -639,54 +527,10 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_gemm(const float* __r
       buf ^= 1;
     });
   }
-  adj_unscale<PREC>(acc, rowmax, b, hh);
-  adjoint_epilogue<NF>(acc, lds, lane, wave, hh, col, b, xw, n_shells, G, A, H2, tw, g);
-}
-
-template <int PREC>
-hipError_t launch_adjoint_gemm_prec(const float* D, const uint4* W, const int* vmask, const unsigned* absmax,
-                                    const unsigned long long* rowmax, int n_shells, long long G, float* A,
-                                    cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st) {
-  dim3 grid((unsigned)(G / kAdjPts), batch);
-#define L2(NF, MBN) hipLaunchKernelGGL((adjoint_gemm<PREC, NF, MBN>), grid, dim3(kAdjThreads), 0, st, D, W, vmask, \
-                                       absmax, rowmax, n_shells, G, A, H2, tw, g)
-#define L(NF) do { if (n_shells > 32) L2(NF, 2); else L2(NF, 1); } while (0)
-  switch (g.N) {
-    case 32: L(32); break;
-    case 64: L(64); break;
-    case 128: L(128); break;
-    case 256: L(256); break;
-    case 512: L(512); break;
-    default: L(0); break;
-  }
-#undef L
-#undef L2
-  return hipGetLastError();
-}
-
-template <int PREC>
-hipError_t launch_adjoint4_gemm_prec(const float* D, const uint4* W, const int* imask, const unsigned* absmax,
-                                     const unsigned long long* rowmax, int n_shells, long long G, float* A,
-                                     cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st) {
-  dim3 grid((unsigned)(G / kAdjPts), batch);
-#define L4(NF, NC) hipLaunchKernelGGL((adjoint4_gemm<PREC, NF, NC>), grid, dim3(kAdjThreads), 0, st, D, W, imask, \
-                                      absmax, rowmax, n_shells, G, A, H2, tw, g)
-#define L(NF)                      \
-  do {                             \
-    if (n_shells <= 32) L4(NF, 2); \
-    else L4(NF, 4);                \
-  } while (0)
-  switch (g.N) {
-    case 32: L(32); break;
-    case 64: L(64); break;
-    case 128: L(128); break;
-    case 256: L(256); break;
-    case 512: L(512); break;
-    default: L(0); break;
-  }
-#undef L
-#undef L4
-  return hipGetLastError();
+  adj_unscale<kFP16>(acc, rowmax, b, hh);
+  auto mfma_row = [&](int j) { return 32 * (j / 16) + 8 * (j % 16 / 4) + 4 * hh + j % 4; };
+  adjoint_epilogue<NF, NC>([&](int pb, int j) { return acc[pb][j / 16][j % 16]; }, mfma_row, lds, wave, col, b, xw,
+                           n_shells, G, A, H2, tw, g);
 }
 
 }  // namespace ps

@@ -122,8 +122,55 @@ hipError_t launch_adjoint_weights(const double* grad, const double* fnorm, const
 // and writes H2 (A must be null); otherwise it writes the fields to A (H2 null).
 inline bool adjoint_fuses_rows(int N) { return N <= 512; }
 hipError_t launch_adjoint_gemm(int prec, const float* D, const uint4* W, const int* vmask, const unsigned* absmax,
-                               const unsigned long long* rowmax, int n_shells, long long G, float* A,
+                               const unsigned long long* rowmax, int n_shells, bool dense, long long G, float* A,
                                cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st);
+// Order 3 in FP32 and BF16, the symmetric form (adjoint_sym.h): partners k in pairs, 32-row
+// chains over the 16-shell chunks of u.  Weight blocks (32 rows x 16 u) of one pair of partners in shell block kb, and pairs
+// staged together (at most 18 blocks of 2 KB per stage).
+__host__ __device__ constexpr int sym_blocks(int kb) { return (kb + 1) * (kb + 1); }
+__host__ __device__ constexpr int sym_stage_pairs(int kb) { return 8 >> kb; }
+__host__ __device__ constexpr int sym_p_chains(int kb) { return kb == 0 ? 1 : kb == 1 ? 0 : kb - 1; }
+// Blocks of all pairs of the shell blocks before kb.
+__host__ __device__ constexpr int sym_base(int kb) {
+  int n = 0;
+  for (int i = 0; i < kb; ++i) n += 8 * sym_blocks(i);
+  return n;
+}
+
+// Position of a block within its pair: the S chains first (uc ascending), then the P
+// chains from the largest uc down, the blocks that the triangle bound empties last, so
+// that the others are contiguous.
+__host__ __device__ constexpr int sym_index(int kb, bool pchain, int M, int t, int uc) {
+  if (!pchain) return t * (kb + 1) + uc;
+  if (kb == 0) return 0;
+  if (kb == 2) return 6 + (2 - uc);
+  if (M == 1) return uc > 0 ? 8 + (3 - uc) : 13;
+  return uc > 1 ? 11 + (3 - uc) : 14 + (1 - uc);
+}
+// Chunks of a P chain that the triangle bound leaves, counted from uc = kb down (the
+// first pair of the block reaches one more: k = 16 kb needs i + j >= k - 2).
+__host__ __device__ constexpr int sym_p_chunks(int kb, int M, bool first) {
+  int n = 0;
+  for (int uc = 0; uc <= kb; ++uc) n += M + uc >= kb - (first ? 2 : 1);
+  return n;
+}
+
+// Order 4 in the symmetric form: blocks stored for partner l (its pairs k / 2 <= l / 2), and
+// of all l < n.
+__host__ __device__ constexpr int sym4_blocks_of(int l) {
+  return sym_base(l / 16) + (l / 2 % 8 + 1) * sym_blocks(l / 16);
+}
+__host__ __device__ constexpr int sym4_blocks(int n) {
+  int s = 0;
+  for (int l = 0; l < n; ++l) s += sym4_blocks_of(l);
+  return s;
+}
+// Blocks of a pair that the kernel multiplies.
+__host__ __device__ constexpr int sym_issued(int kb, bool first, bool dense) {
+  int n = kb > 0 ? 2 * (kb + 1) : 0;
+  for (int M = 0; M < sym_p_chains(kb); ++M) n += dense ? kb + 1 : sym_p_chunks(kb, M, first);
+  return n;
+}
 // Order 4 (n_shells <= kAdj4MaxShells): W4[b][item (w, v <= w)][uc][mb][hi, lo][lane],
 // item = w (w + 1) / 2 + v, over NC = 2 chunks of u and one 32-row block of m up to 32
 // shells, NC = 4 chunks and two blocks above.
@@ -136,8 +183,8 @@ __host__ __device__ constexpr int adj4_words_per_item(int n_shells) {
 hipError_t launch_adjoint4_weights(const double* grad, const double* fnorm, const int* lookup, int n_shells,
                                    int n_closing, int prec, const unsigned* absmax, unsigned long long* rowmax,
                                    uint4* W, int batch, hipStream_t st);
-hipError_t launch_adjoint4_gemm(int prec, const float* D, const uint4* W, const int* imask, const unsigned* absmax,
-                                const unsigned long long* rowmax, int n_shells, long long G, float* A,
+hipError_t launch_adjoint4_gemm(int prec, const float* D, const uint4* W, const int* imask, const int* pmask,
+                                const unsigned* absmax, const unsigned long long* rowmax, int n_shells, long long G, float* A,
                                 cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st);
 
 // util.hip

@@ -108,12 +108,13 @@ struct polyspec_plan_s {
   std::vector<int> pair_uv;
   // shell-block aligned order-3 schedule (FP16 split)
   std::vector<int> wmask_host;     // adjoint: per v, bits 2 uc + mb of weight blocks
+  std::vector<int> pmask_host;     // order-4 adjoint: per l, the pairs of partners with a weight
   bool jsched = false;
   int n_tiles_j = 0, ksteps_j = 0, n_chunks_j = 0;
 
   // device tables
   DevBuf tw32, shell_q, qmax_d, pairs_d, slots_d, slot_lane_d, slot_tile_d, slot_blk_d, ent_d, bins_d, fnorm_d, lookup_d,
-      wmask_d, flag_d;
+      wmask_d, pmask_d, flag_d;
   DevBuf jtile_d, jmask_d, ent_j_d;
   // order 4 with more pair blocks than one workgroup's LDS holds: each tile group's own
   // pair blocks (global ids, kMaxPairBlocksHost per group) and their count
@@ -1009,8 +1010,13 @@ polyspec_status build_plan(polyspec_plan_s* p) {
     // skips items without any, and blocks of m without any
     const int nb = p->nb;
     std::vector<int> imask(nb * (nb + 1) / 2, 0);
+    // the symmetric form (FP32, BF16): partner pairs k / 2 of l = t[3] with a weight; a term
+    // within shell block 0 is also a row of its middle side's partner
+    std::vector<int> pmask(nb, 0);
     for (size_t k = 0; k < p->closing.size(); ++k) {
       const int* t = &p->cl_bins[k * 4];
+      pmask[t[3]] |= 1 << (t[2] / 2);
+      if (t[2] < 16) pmask[t[3]] |= 1 << (t[1] / 2);
       for (int pos = 0; pos < 4; ++pos) {
         int rest[3], r = 0;
         for (int j = 0; j < 4; ++j)
@@ -1020,6 +1026,8 @@ polyspec_status build_plan(polyspec_plan_s* p) {
     }
     p->wmask_host = imask;
     PS_TRY(upload(p, &p->wmask_d, imask));
+    p->pmask_host = pmask;
+    PS_TRY(upload(p, &p->pmask_d, pmask));
   }
   return POLYSPEC_OK;
 }
@@ -1033,7 +1041,7 @@ void release(polyspec_plan_s* p) {
   for (hipEvent_t e : p->ev_pool) (void)hipEventDestroy(e);
   p->ev_pool.clear();
   DevBuf* bufs[] = {&p->tw32, &p->shell_q, &p->qmax_d, &p->pairs_d, &p->slots_d, &p->slot_lane_d, &p->slot_tile_d, &p->slot_blk_d, &p->ent_d,
-                    &p->bins_d, &p->fnorm_d, &p->lookup_d, &p->wmask_d, &p->flag_d, &p->jtile_d, &p->jmask_d,
+                    &p->bins_d, &p->fnorm_d, &p->lookup_d, &p->wmask_d, &p->pmask_d, &p->flag_d, &p->jtile_d, &p->jmask_d,
                     &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->grp_blk_d, &p->grp_nblk_d,
                     &p->own_ws};
   for (DevBuf* b : bufs) dev_free(b);
@@ -1419,12 +1427,12 @@ polyspec_status polyspec_backward(polyspec_plan_t p, const double* d_grad_out, v
     if (p->order == 3)
       PS_TIMED(p, POLYSPEC_PH_ADJ_GEMM,
                ps::launch_adjoint_gemm(aprec, p->D, (const uint4*)p->W, (const int*)p->wmask_d.p, p->absmax,
-                                       p->rowmax, p->nb, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
+                                       p->rowmax, p->nb, !p->alias_free, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
                                        gk, p->batch, st));
     else
       PS_TIMED(p, POLYSPEC_PH_ADJ_GEMM,
-               ps::launch_adjoint4_gemm(aprec, p->D, (const uint4*)p->W, (const int*)p->wmask_d.p, p->absmax,
-                                        p->rowmax, p->nb, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
+               ps::launch_adjoint4_gemm(aprec, p->D, (const uint4*)p->W, (const int*)p->wmask_d.p,
+                                        (const int*)p->pmask_d.p, p->absmax, p->rowmax, p->nb, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
                                         gk, p->batch, st));
     if (!fused) PS_TIMED(p, POLYSPEC_PH_ADJ_Q3, ps::launch_r2c_q3(p->A, p->H2, tw, gk, nz, st));
     PS_TIMED(p, POLYSPEC_PH_ADJ_Q2, ps::launch_r2c_q2(p->H2, H1x, tw, gk, nz, st));
@@ -1537,34 +1545,41 @@ polyspec_status polyspec_issued_flops(polyspec_plan_t p, int32_t phase, double* 
     const bool aligned = p->jsched && p->prec == POLYSPEC_SPLIT_FP16 && p->ksteps_j % 4 == 0;
     *flops = (aligned ? p->n_tiles_j : p->n_tiles) * 512.0 * terms * pts;
   } else if (phase == POLYSPEC_PH_ADJ_GEMM && p->order == 4 && p->nb <= ps::kAdj4MaxShells) {
-    // per item (w, v): the 16-shell chunks of u <= v, for each 32-row block of m with a
-    // weight (the only block up to 32 shells)
+    // 32 x 32 x 16 products per 32 grid points.  FP16: per item (w, v) the 16-shell chunks
+    // of u <= v, for each 32-row block of m with a weight (the only block up to 32
+    // shells); otherwise the chains of each pair of partners with a weight.
     double blocks = 0.0;
-    const int mbn = p->nb > 32 ? 2 : 1;
-    for (int w = 0; w < p->nb; ++w)
-      for (int v = 0; v <= w; ++v) {
-        const int mask = p->wmask_host[w * (w + 1) / 2 + v];
-        if (!mask) continue;
-        for (int mb = 0; mb < mbn; ++mb)
-          if (mbn == 1 || (mask & (0x55 << mb))) blocks += v / 16 + 1;
-      }
+    if (p->prec == POLYSPEC_SPLIT_FP16 && !p->streamed) {
+      const int mbn = p->nb > 32 ? 2 : 1;
+      for (int w = 0; w < p->nb; ++w)
+        for (int v = 0; v <= w; ++v) {
+          const int mask = p->wmask_host[w * (w + 1) / 2 + v];
+          if (!mask) continue;
+          for (int mb = 0; mb < mbn; ++mb)
+            if (mbn == 1 || (mask & (0x55 << mb))) blocks += v / 16 + 1;
+        }
+    } else {
+      for (int l = 0; l < p->nb; ++l)
+        for (int pair = 0; pair < 32; ++pair)
+          if ((p->pmask_host[l] >> pair) & 1) blocks += ps::sym_blocks(pair / 8);
+    }
     *flops = blocks * 32.0 * 32.0 * 16.0 * 2.0 / 32.0 * terms * pts;
   } else if (phase == POLYSPEC_PH_ADJ_GEMM && p->order == 3 && has_adjoint(p)) {
-    // per partner shell v, 32 x 32 x 16 products per 32 grid points: for v >= 16 in FP32
-    // and BF16 every (16-shell chunk u <= v, 32-row block of m); otherwise the blocks
-    // that hold a weight (the adjoint's arithmetic is that of backward())
-    const bool fp16 = p->prec == POLYSPEC_SPLIT_FP16 && !p->streamed;
-    const int mbn = p->nb > 32 ? 2 : 1;
+    // 32 x 32 x 16 products per 32 grid points (the adjoint's arithmetic is that of
+    // backward()): FP16, per partner shell v the blocks that hold a weight; otherwise the
+    // chains of each pair of partners, in stages of sym_stage_pairs pairs
     double blocks = 0.0;
-    for (int v = 0; v < p->nb; ++v) {
-      const int mask = p->wmask_host[v];
-      if (!mask) continue;
-      if (!fp16 && v >= 16) {
-        blocks += mbn * (v / 16 + 1);
-        continue;
-      }
-      for (int mb = 0; mb < mbn; ++mb)
-        for (int uc = 0; uc <= v / 16; ++uc) blocks += (mask >> (2 * uc + mb)) & 1;
+    if (p->prec == POLYSPEC_SPLIT_FP16 && !p->streamed) {
+      const int mbn = p->nb > 32 ? 2 : 1;
+      for (int v = 0; v < p->nb; ++v)
+        for (int mb = 0; mb < mbn; ++mb)
+          for (int uc = 0; uc <= v / 16; ++uc) blocks += (p->wmask_host[v] >> (2 * uc + mb)) & 1;
+    } else {
+      for (int kb = 0; 16 * kb < p->nb; ++kb)
+        for (int pair = 0; pair < 8; ++pair) {
+          const int stage0 = pair / ps::sym_stage_pairs(kb) * ps::sym_stage_pairs(kb);
+          if (16 * kb + 2 * stage0 < p->nb) blocks += ps::sym_issued(kb, pair == 0, !p->alias_free);
+        }
     }
     *flops = blocks * 32.0 * 32.0 * 16.0 * 2.0 / 32.0 * terms * pts;
   }
