@@ -4,28 +4,42 @@ namespace ps {
 
 // ---------------------------------------------------------------------------
 // Order 3, pair blocks aligned to shell blocks (FP16 split).
-//   S[(i, j), k] = sum_x d_i d_j d_k  for i in shell block ib, one shell j, k in block kb.
-// For j in the first two shell blocks the A operand of tile (ib, j, kb) is the
-// shell-block operand of ib times the row of shell j (the same for all 16 rows); for
-// j in the last two, where fewer blocks kb >= jb than ib <= jb exist, the B operand
-// of kb is scaled by d_j instead.  Either way every operand of a 32-point step comes
-// from the four shell-block operands held in registers plus two LDS reads per j (all
-// 16 rows of a point group read one word).  Wave w owns j = w + 8 q and the
-// tiles (ib <= jb = q / 2, kb >= jb), one static accumulator each; a per-wave mask
-// says which of them hold a candidate tuple.  Rows i > j of the diagonal block are
-// computed and never read.
+//   S[i, j, k] = sum_x d_i d_j d_k, i <= j <= k, by the 16-shell block jb of the middle shell.
+// Every 16 x 16 tile is a product operand (16 rows d_p d_j) times the plain operand of a
+// shell block held in registers.  What fixes the rows of the product operand:
+//   jb = 0, 1, i in block jb:  rows i <= j, columns k >= jb's block;
+//   jb = 2, 3, k in block jb:  rows k >= j, columns i <= jb's block;
+//   jb = 1, i in block 0:      rows i, columns k;
+//   jb = 2, k in block 3:      rows k, columns i.
+// In the first two a shell j fills only part of the 16 rows, so two shells whose rows add
+// up to 16 share one operand (rows from either end): j = a and 14 - a of the block (for
+// the second kind mirrored, 15 - a and 1 + a), a = 0..6 for wave a, and the full j = 15
+// (j = 0) for wave 7.  The half-full j = 7 (j = 8) of two blocks share a ninth operand,
+// whose four columns blocks go to waves 0 to 3, two each.  64 unit shells take 186 tiles
+// instead of 260 with one operand per j, and 66 operands formed per step instead of 96
+// (512^3: 47.5 ms before).  Both rows of a product come from LDS words at lane-dependent
+// slots, the rest of a 32-point step from registers.  A per-wave mask says which tiles
+// hold a candidate tuple.
 // ---------------------------------------------------------------------------
 constexpr int kJThreads = 64 * kJWaves;
-static_assert(jslot(7, 3, 3) + 1 == kJSlots, "slot numbering");
 static_assert(kSlots == kSlotsHost && kSlots4 == kSlots4Host && kSlots56 == kSlots56Host && kSlots6 == kSlots6Host &&
                   kSlotsMax == kSlotsMaxHost && 2 * kSlots56 <= kSlotsMax && kMaxBlk == kMaxBlkHost &&
                   kCtrWaves == kCtrWavesHost,
               "host and device tile tables agree");
 
 
-template <int PREC>
+// NBLK: 16-shell blocks of the plan.  ALL: every wave uses every kind of product operand, so
+// that a step is straight-line code; otherwise the unused ones are skipped, one branch each
+// (512^3, 64 shells: 34.7 against 36.3 ms; a multipole plan of 46 fields, half of whose
+// operands are unused: 0.34 against 0.27 ms with the branches).
+//
+// 512^3, 64 shells (the start of these measurements: 47.5 ms): 37.9 ms with shared operands,
+// 34.7 with the next step's fields split in the middle of the step instead of before its
+// barrier.  What is left: without staging 28 ms, without forming products 29.7, the matrix
+// products alone 20.  128^3 x 8, 24 shells: 1.99 -> 0.98 ms.
+template <int NBLK, bool ALL>
 __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
-  static_assert(PREC == kFP16, "shell-block aligned contraction is implemented for the FP16 split");
+  constexpr int PREC = kFP16;
   __shared__ uint4 opHi[2][2][kMaxBlk][64];   // [buffer][K-step][shell block][lane]
   __shared__ uint4 opLo[2][2][kMaxBlk][64];
   __shared__ float lds_scale[kMaxBlk * 16];
@@ -48,118 +62,130 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
   }
   __syncthreads();
 
-  // staging: float4 #f of the (64 shells x 64 points) slice, f = tid and tid + kJThreads
-  const float* Db = p.D + (size_t)b * p.n_shells * p.G;
+  // staging: float4 #f of the (16 NBLK shells x 64 points) slice, f = tid, tid + kJThreads;
+  // rows past the plan's shells reread shell 0 and store zeros
+  constexpr int kF4 = (NBLK + 1) / 2;   // float4 per thread per stage
   const long long x_base = (long long)chunk * p.ksteps * kKStep;
-  constexpr int kF4 = 64 * kKStep / 4 / kJThreads;   // float4 per thread per stage
-  int st_row[kF4], st_col[kF4];
+  const float* src[kF4];
+  float st_scale[kF4];
+  bool st_on[kF4];
 #pragma unroll
   for (int f = 0; f < kF4; ++f) {
-    const int idx = tid + f * kJThreads;
-    st_row[f] = idx >> 4;
-    st_col[f] = (idx & 15) * 4;
+    const int idx = tid + f * kJThreads, row = idx >> 4;
+    st_on[f] = row < p.n_shells;
+    st_scale[f] = lds_scale[row];
+    src[f] = p.D + ((size_t)b * p.n_shells + (st_on[f] ? row : 0)) * p.G + x_base + (idx & 15) * 4;
   }
-  auto stage_store = [&](int buf, int f, float4 v) {
-    const int row = st_row[f], col = st_col[f];
-    const float sc = lds_scale[row];
-    v = make_float4(v.x * sc, v.y * sc, v.z * sc, v.w * sc);
+  float4 pre[kF4];
+  auto stage_load = [&](int ks) {
+#pragma unroll
+    for (int f = 0; f < kF4; ++f) pre[f] = *reinterpret_cast<const float4*>(src[f] + (size_t)ks * kKStep);
+  };
+  auto stage_store = [&](int buf, int f) {
+    const int idx = tid + f * kJThreads, row = idx >> 4, col = (idx & 15) * 4;
+    const float sc = st_scale[f];
+    const float4 v = st_on[f] ? make_float4(pre[f].x * sc, pre[f].y * sc, pre[f].z * sc, pre[f].w * sc)
+                              : make_float4(0.f, 0.f, 0.f, 0.f);
     uint2 hi, lo;
     split4<PREC>(v, 1.f, hi, lo);
     const int h = col >> 5, kb = row >> 4, ln = op_slot((((col & 31) >> 3) << 4) | (row & 15)), half = (col >> 2) & 1;
     reinterpret_cast<uint2*>(&opHi[buf][h][kb][ln])[half] = hi;
     reinterpret_cast<uint2*>(&opLo[buf][h][kb][ln])[half] = lo;
   };
-  float4 pre[kF4];
+  stage_load(0);
 #pragma unroll
-  for (int f = 0; f < kF4; ++f) {
-    pre[f] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (st_row[f] < p.n_shells)
-      pre[f] = *reinterpret_cast<const float4*>(Db + (size_t)st_row[f] * p.G + x_base + st_col[f]);
-  }
-#pragma unroll
-  for (int f = 0; f < kF4; ++f)
-    if (st_row[f] < p.n_shells) stage_store(0, f, pre[f]);
+  for (int f = 0; f < kF4; ++f) stage_store(0, f);
   __syncthreads();
 
-  const unsigned m0 = __builtin_amdgcn_readfirstlane(p.slot_mask[2 * wave]);
-  const unsigned m1 = __builtin_amdgcn_readfirstlane(p.slot_mask[2 * wave + 1]);
+  const unsigned m0 = __builtin_amdgcn_readfirstlane(p.slot_mask[wave]);
+  // LDS words of the two rows of a product, by kind (block offsets are added as constants)
+  const int row = lane & 15, grp = lane & 0x30;
+  const int a = wave < 7 ? wave : 15;
+  const bool lead = row <= a;                                   // rows of the first shell of the pair
+  const int ap = op_slot(grp | (lead ? row : 15 - row)), aj = op_slot(grp | (lead ? a : 14 - a));
+  const int bp = op_slot(grp | (lead ? 15 - row : row)), bj = op_slot(grp | (lead ? 15 - a : 1 + a));
+  const int uj[2] = {op_slot(grp | wave), op_slot(grp | (wave + 8))};   // single shells j = wave, wave + 8
+  const bool low = row < 8;
+  const int xblk = wave < 2 ? (low ? 0 : 1) : (low ? 3 : 2);
+  const int xp = 64 * xblk + op_slot(grp | (low == (wave < 2) ? row : 15 - row));
+  const int xj = 64 * xblk + op_slot(grp | (wave < 2 ? 7 : 8));
   f32x4 acc[kJSlots];
 #pragma unroll
   for (int s = 0; s < kJSlots; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int ks = 0; ks < p.ksteps; ++ks) {
     const int cur = ks & 1;
-    if (ks + 1 < p.ksteps) {
-#pragma unroll
-      for (int f = 0; f < kF4; ++f)
-        if (st_row[f] < p.n_shells)
-          pre[f] = *reinterpret_cast<const float4*>(Db + (size_t)st_row[f] * p.G + x_base + (ks + 1) * kKStep +
-                                                    st_col[f]);
-    }
+    stage_load(min(ks + 1, p.ksteps - 1));   // the last step stores a copy that nothing reads
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-    // the slot masks are re-read from SGPRs every half step (scalar bit tests) instead
-    // of being kept as 40 precomputed lane masks, which would not fit in the SGPRs: with
-    // one re-read per step the compiler still kept the 40 conditions of both halves and
-    // spilled them into VGPR lanes (51.0 -> 47.5 ms for the 512^3 contraction)
-    unsigned mm0 = m0, mm1 = m1;
-    asm volatile("" : "+s"(mm0), "+s"(mm1));
-    mm0 = __builtin_amdgcn_readfirstlane(mm0);
-    mm1 = __builtin_amdgcn_readfirstlane(mm1);
-    auto active = [&](int s) { return ((s < 32 ? mm0 >> s : mm1 >> (s - 32)) & 1u) != 0; };
-      Operand<PREC> Bop[kMaxBlk];
+      // the mask is re-read from an SGPR every half step (scalar bit tests) instead of being
+      // kept as precomputed lane masks, which would spill into VGPR lanes
+      unsigned mm = m0;
+      asm volatile("" : "+s"(mm));
+      mm = __builtin_amdgcn_readfirstlane(mm);
+      const uint4* hi = &opHi[cur][h][0][0];
+      const uint4* lo = &opLo[cur][h][0][0];
+      auto words = [&](int i) { return op_from_words<PREC>(hi[i], lo[i]); };
+      Operand<PREC> Bop[NBLK];
 #pragma unroll
-      for (int kb = 0; kb < kMaxBlk; ++kb) Bop[kb] = op_from_words<PREC>(opHi[cur][h][kb][my_slot], opLo[cur][h][kb][my_slot]);
-      static_for<8>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        constexpr int jb = q / 2;
-        const int j = wave + kJWaves * q;
-        if (j >= p.n_shells) return;
-        const int rj = op_slot((lane & 0x30) | (j & 15));
-        const Operand<PREC> dj = op_from_words<PREC>(opHi[cur][h][jb][rj], opLo[cur][h][jb][rj]);
-        if constexpr (jb <= 1) {
-          // few blocks ib <= jb: scale the A side, A = (d_i d_j) rows
-          static_for<jb + 1>([&](auto ibc) {
-            constexpr int ib = decltype(ibc)::value;
-            bool any = false;
-            static_for<kMaxBlk - jb>([&](auto kc) { any = any || active(jslot(q, ib, jb + decltype(kc)::value)); });
-            if (!any) return;
-            const Operand<PREC> A = pair_f16(Bop[ib], dj);
-            static_for<kMaxBlk - jb>([&](auto kc) {
-              constexpr int kb = jb + decltype(kc)::value;
-              if (active(jslot(q, ib, kb))) mma<PREC>(acc[jslot(q, ib, kb)], A, Bop[kb]);
-            });
-          });
-        } else {
-          // few blocks kb >= jb: scale the B side, B = (d_j d_k) columns; same sums
-          static_for<kMaxBlk - jb>([&](auto kc) {
-            constexpr int kb = jb + decltype(kc)::value;
-            bool any = false;
-            static_for<jb + 1>([&](auto ibc) { any = any || active(jslot(q, decltype(ibc)::value, kb)); });
-            if (!any) return;
-            const Operand<PREC> Bs = pair_f16(Bop[kb], dj);
-            static_for<jb + 1>([&](auto ibc) {
-              constexpr int ib = decltype(ibc)::value;
-              if (active(jslot(q, ib, kb))) mma<PREC>(acc[jslot(q, ib, kb)], Bop[ib], Bs);
+      for (int kb = 0; kb < NBLK; ++kb) Bop[kb] = words(64 * kb + my_slot);
+      // Slots s0 .. s0 + CNT - 1: the product operand times the blocks x0, x0 + 1, ... of the
+      // plan, the three products of the split in turn, so that none waits for the one before
+      // it.
+      auto tiles = [&](auto s0c, auto cntc, auto x0c, auto&& form) {
+        constexpr int s0 = decltype(s0c)::value, x0 = decltype(x0c)::value;
+        constexpr int CNT = decltype(cntc)::value < NBLK - x0 ? decltype(cntc)::value : NBLK - x0;
+        if constexpr (CNT > 0) {
+          if (!ALL && (mm & (((1u << CNT) - 1) << s0)) == 0) return;
+          const Operand<PREC> A = form();
+          static_for<3>([&](auto term) {
+            static_for<CNT>([&](auto c) {
+              mma_term<decltype(term)::value>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
             });
           });
         }
+      };
+      // one tile that the triangle bound empties for all but the last shell of a block
+      auto corner = [&](auto sc, auto xc, auto&& form) {
+        constexpr int s0 = decltype(sc)::value, x = decltype(xc)::value;
+        if constexpr (x < NBLK)
+          if ((mm >> s0) & 1) mma<PREC>(acc[s0], form(), Bop[x]);
+      };
+#define PS_C(v) std::integral_constant<int, v>{}
+      auto diag0 = [&] { return pair_f16(words(ap), words(aj)); };
+      tiles(PS_C(kJDiag0), PS_C(2), PS_C(0), diag0);
+      tiles(PS_C(kJDiag1), PS_C(3), PS_C(1), [&] { return pair_f16(words(64 + ap), words(64 + aj)); });
+      if constexpr (NBLK > 2)
+        tiles(PS_C(kJDiag2), PS_C(3), PS_C(0), [&] { return pair_f16(words(128 + bp), words(128 + bj)); });
+      if constexpr (NBLK > 3)
+        tiles(PS_C(kJDiag3), PS_C(4), PS_C(0), [&] { return pair_f16(words(192 + bp), words(192 + bj)); });
+      // the next step's fields, split under the products
+      if (h == 1) stage_store(cur ^ 1, 0);
+      static_for<2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        if (h == 1 && q == 1 && kF4 == 2) stage_store(cur ^ 1, kF4 - 1);
+        tiles(PS_C(kJLow + 3 * q), PS_C(2), PS_C(1), [&] { return pair_f16(Bop[0], words(64 + uj[q])); });
+        if constexpr (NBLK > 3)
+          tiles(PS_C(kJHigh + 3 * q), PS_C(3), PS_C(0), [&] { return pair_f16(Bop[3], words(128 + uj[q])); });
       });
-    }
-    if (ks + 1 < p.ksteps) {
-#pragma unroll
-      for (int f = 0; f < kF4; ++f)
-        if (st_row[f] < p.n_shells) stage_store(cur ^ 1, f, pre[f]);
+      if ((mm >> kJShared) != 0) {
+        if (wave & 1) tiles(PS_C(kJShared), PS_C(2), PS_C(2), [&] { return pair_f16(words(xp), words(xj)); });
+        else tiles(PS_C(kJShared), PS_C(2), PS_C(0), [&] { return pair_f16(words(xp), words(xj)); });
+      }
+      corner(PS_C(kJDiag0 + 2), PS_C(2), diag0);
+      corner(PS_C(kJDiag0 + 3), PS_C(3), diag0);
+      corner(PS_C(kJLow + 2), PS_C(3), [&] { return pair_f16(Bop[0], words(64 + uj[0])); });
+      corner(PS_C(kJLow + 5), PS_C(3), [&] { return pair_f16(Bop[0], words(64 + uj[1])); });
+#undef PS_C
     }
     __syncthreads();
   }
 
-  auto active = [&](int s) { return ((s < 32 ? m0 >> s : m1 >> (s - 32)) & 1u) != 0; };
   const int* my_tiles = p.tile_of_slot + wave * kJSlots;
   float* out = p.partials + ((size_t)b * p.n_chunks + chunk) * (size_t)p.n_tiles * 256;
 #pragma unroll
   for (int s = 0; s < kJSlots; ++s) {
-    if (!active(s)) continue;
+    if (!((m0 >> s) & 1)) continue;
     *reinterpret_cast<f32x4*>(out + (size_t)my_tiles[s] * 256 + 4 * lane) = acc[s];
   }
 }
@@ -167,7 +193,15 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
 hipError_t launch_contract_j3(int prec, const CtrJParams& p, int batch, hipStream_t st) {
   if (prec != kFP16) return hipErrorInvalidValue;
   dim3 grid(p.n_chunks, 1, batch);
-  hipLaunchKernelGGL(contract_j3<kFP16>, grid, dim3(kJThreads), 0, st, p);
+#define L(NBLK, ALL) hipLaunchKernelGGL((contract_j3<NBLK, ALL>), grid, dim3(kJThreads), 0, st, p)
+  switch (p.n_blk) {
+    case 1: L(1, false); break;
+    case 2: L(2, false); break;
+    case 3: if (p.all_used) L(3, true); else L(3, false); break;
+    case 4: if (p.all_used) L(4, true); else L(4, false); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef L
   return hipGetLastError();
 }
 

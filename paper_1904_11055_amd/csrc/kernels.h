@@ -75,21 +75,43 @@ constexpr int kCntStageHost = 32;
 
 hipError_t launch_contract(int prec, int order, const CtrParams& p, int n_groups, int batch, hipStream_t st);
 
-// Order 3 with pair blocks aligned to shell blocks: wave w of kJWaves owns the shells
-// j = w + kJWaves q (q = 0..7, shell block jb = q / 2) and the tiles (ib <= jb, kb >= jb)
-// of each, at most kJSlots per wave, numbered by jslot().
+// Order 3 with products aligned to shell blocks (contract_j3.hip): the slots of a wave, one
+// 16 x 16 tile each, by the kind of product operand and the plain operand's block.
 constexpr int kJWaves = 8;
-constexpr int kJSlots = 40;
-__host__ __device__ constexpr int jslot(int q, int ib, int kb) {
-  int s = 0;
-  for (int qq = 0; qq < q; ++qq) s += (qq / 2 + 1) * (4 - qq / 2);
-  return s + ib * (4 - q / 2) + (kb - q / 2);
+constexpr int kJDiag0 = 0;     // j and i in block 0: columns k of blocks 0..3
+constexpr int kJDiag1 = 4;     // j and i in block 1: columns k of blocks 1..3
+constexpr int kJDiag2 = 7;     // j and k in block 2: columns i of blocks 0..2
+constexpr int kJDiag3 = 10;    // j and k in block 3: columns i of blocks 0..3
+constexpr int kJLow = 14;      // j = 16 + w + 8 q, i in block 0: slots 3 q + columns k of blocks 1..3
+constexpr int kJHigh = 20;     // j = 32 + w + 8 q, k in block 3: slots 3 q + columns i of blocks 0..2
+constexpr int kJShared = 26;   // the half-full shells of blocks 0, 1 (waves 0, 1) and 2, 3 (waves 2, 3)
+constexpr int kJSlots = 28;
+struct JPlace {
+  int wave, slot, row, col;
+};
+// Where the candidate i <= j <= k (0-based) is accumulated.
+inline JPlace jplace(int i, int j, int k) {
+  const int ib = i / 16, jb = j / 16, kb = k / 16, il = i % 16, jl = j % 16, kl = k % 16;
+  if (jb == 1 && ib == 0) return {jl % 8, kJLow + 3 * (jl / 8) + kb - 1, il, kl};
+  if (jb == 2 && kb == 3) return {jl % 8, kJHigh + 3 * (jl / 8) + ib, kl, il};
+  if (jb <= 1) {               // rows i <= j
+    if (jl == 7) return {kb / 2, kJShared + kb % 2, jb == 0 ? il : 15 - il, kl};
+    const int slot = jb == 0 ? kJDiag0 + kb : kJDiag1 + kb - 1;
+    if (jl < 7 || jl == 15) return {jl < 7 ? jl : 7, slot, il, kl};
+    return {14 - jl, slot, 15 - il, kl};
+  }
+  const int jm = 15 - jl;      // rows k >= j, mirrored
+  if (jm == 7) return {2 + ib / 2, kJShared + ib % 2, jb == 3 ? 15 - kl : kl, il};
+  const int slot = (jb == 2 ? kJDiag2 : kJDiag3) + ib;
+  if (jm < 7 || jm == 15) return {jm < 7 ? jm : 7, slot, 15 - kl, il};
+  return {14 - jm, slot, kl, il};
 }
 struct CtrJParams {
   const float* D;
   const unsigned* absmax;
   const int* tile_of_slot;   // [kJWaves][kJSlots]: compact tile id, or -1
-  const unsigned* slot_mask; // [kJWaves][2]: bit s set when slot s holds a tile
+  const unsigned* slot_mask; // [kJWaves]: bit s set when slot s holds a tile
+  bool all_used;             // every wave has a tile of every kind of product operand
   float* partials;
   long long G;
   int n_shells;

@@ -97,6 +97,12 @@ __device__ __forceinline__ void mma(f32x4& acc, const Operand<PREC>& a, const Op
   }
 }
 
+// One of the three products of the FP16 split: hi hi, hi lo, lo hi.
+template <int TERM>
+__device__ __forceinline__ void mma_term(f32x4& acc, const Operand<kFP16>& a, const Operand<kFP16>& b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(TERM == 2 ? a.lo : a.hi, TERM == 1 ? b.lo : b.hi, acc, 0, 0, 0);
+}
+
 // Lane l of a 16x16x32 operand holds row (l % 16) at grid points 8 (l / 16) .. +7
 // of the current 32-point stage (the same K mapping for both operands).
 __device__ __forceinline__ void load_row8(const float* lds_row, int g, float (&x)[8]) {

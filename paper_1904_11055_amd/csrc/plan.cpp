@@ -109,7 +109,7 @@ struct polyspec_plan_s {
   // shell-block aligned order-3 schedule (FP16 split)
   std::vector<int> wmask_host;     // adjoint: per v, bits 2 uc + mb of weight blocks
   std::vector<int> pmask_host;     // order-4 adjoint: per l, the pairs of partners with a weight
-  bool jsched = false;
+  bool jsched = false, j_all_used = false;
   int n_tiles_j = 0, ksteps_j = 0, n_chunks_j = 0;
 
   // device tables
@@ -641,31 +641,41 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   return POLYSPEC_OK;
 }
 
-// Order 3, shell-block aligned schedule: candidate (i <= j <= k) lives in slot
-// jslot(j / 8, i / 16, k / 16) of wave j % 8; used slots get compact tile ids.
+// Order 3, shell-block aligned schedule: candidate (i <= j <= k) lives in the wave, slot and
+// tile entry of jplace(); used slots get compact tile ids.
 polyspec_status build_jsched(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   p->jsched = p->order == 3 && p->n_blk <= ps::kMaxBlkHost;
   if (!p->jsched) return POLYSPEC_OK;
   const size_t nc = p->cand.size() / 3;
   std::vector<int> tile((size_t)ps::kJWaves * ps::kJSlots, -1);
-  std::vector<unsigned> mask((size_t)ps::kJWaves * 2, 0u);
-  auto slot_of = [&](const int* t) {
-    return (t[1] % ps::kJWaves) * ps::kJSlots + ps::jslot(t[1] / ps::kJWaves, t[0] / 16, t[2] / 16);
-  };
-  for (size_t c = 0; c < nc; ++c) tile[slot_of(&p->cand[c * 3])] = 0;
+  std::vector<unsigned> mask(ps::kJWaves, 0u);
+  auto place = [&](size_t c) { return ps::jplace(p->cand[c * 3], p->cand[c * 3 + 1], p->cand[c * 3 + 2]); };
+  for (size_t c = 0; c < nc; ++c) {
+    const ps::JPlace w = place(c);
+    tile[w.wave * ps::kJSlots + w.slot] = 0;
+  }
   int id = 0;
   for (int w = 0; w < ps::kJWaves; ++w)
     for (int s = 0; s < ps::kJSlots; ++s) {
       int& t = tile[(size_t)w * ps::kJSlots + s];
       if (t < 0) continue;
       t = id++;
-      mask[2 * w + s / 32] |= 1u << (s % 32);
+      mask[w] |= 1u << s;
     }
   p->n_tiles_j = id;
+  // slots of each kind (the corners of contract_j3 left out), as far as the plan's blocks go
+  p->j_all_used = true;
+  for (int w = 0; w < ps::kJWaves; ++w) {
+    const unsigned kinds[] = {0x3u << ps::kJDiag0, 0x7u << ps::kJDiag1, 0x3u << ps::kJLow, 0x3u << (ps::kJLow + 3),
+                              0x7u << ps::kJDiag2, 0xfu << ps::kJDiag3, 0x7u << ps::kJHigh,
+                              0x7u << (ps::kJHigh + 3)};
+    const int n_kinds = p->n_blk == 4 ? 8 : p->n_blk == 3 ? 5 : p->n_blk == 2 ? 4 : 1;
+    for (int k = 0; k < n_kinds; ++k) p->j_all_used = p->j_all_used && (mask[w] & kinds[k]) != 0;
+  }
   ent_of_cand->resize(nc);
   for (size_t c = 0; c < nc; ++c) {
-    const int* t = &p->cand[c * 3];
-    (*ent_of_cand)[c] = tile[slot_of(t)] * 256 + tile_entry(t[0] % 16, t[2] % 16);
+    const ps::JPlace w = place(c);
+    (*ent_of_cand)[c] = tile[w.wave * ps::kJSlots + w.slot] * 256 + tile_entry(w.row, w.col);
   }
   PS_TRY(upload(p, &p->jtile_d, tile));
   PS_TRY(upload(p, &p->jmask_d, mask));
@@ -1237,6 +1247,7 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     jp.absmax = p->absmax;
     jp.tile_of_slot = (const int*)p->jtile_d.p;
     jp.slot_mask = (const unsigned*)p->jmask_d.p;
+    jp.all_used = p->j_all_used;
     jp.partials = p->partials;
     jp.G = launch_points(p);
     jp.n_shells = p->nb;
