@@ -100,9 +100,10 @@ __device__ __forceinline__ void adj_store_weight(uint4* base, int ln, int r, dou
     dst[r & 3] = (float)w;
   } else if (prec == kBF16) {
     const float x = (float)w;
-    const __bf16 h = (__bf16)x;   // rounded to nearest, like the field operands
-    reinterpret_cast<unsigned short*>(&base[ln])[r] = __builtin_bit_cast(unsigned short, h);
-    reinterpret_cast<unsigned short*>(&base[64 + ln])[r] = __builtin_bit_cast(unsigned short, (__bf16)(x - (float)h));
+    const unsigned bits = __float_as_uint(x);
+    const float h = __uint_as_float(bits & 0xffff0000u);
+    reinterpret_cast<unsigned short*>(&base[ln])[r] = (unsigned short)(bits >> 16);
+    reinterpret_cast<unsigned short*>(&base[64 + ln])[r] = __builtin_bit_cast(unsigned short, (__bf16)(x - h));
   } else {
     const float x = (float)w;
     const _Float16 h = (_Float16)x;

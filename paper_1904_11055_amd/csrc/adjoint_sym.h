@@ -42,24 +42,6 @@ constexpr size_t sym_lds_bytes() {
   return adj_fft_lds_bytes<NF, KB>() > stage ? adj_fft_lds_bytes<NF, KB>() : stage;
 }
 
-// The fields of a chunk as a B operand.  BF16: hi is rounded to nearest, not truncated, so
-// that the dropped lo lo products are smaller and of either sign.
-template <int PREC>
-__device__ __forceinline__ Operand<PREC> sym_operand(const float (&x)[8]) {
-  if constexpr (PREC == kBF16) {
-    Operand<kBF16> o;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const __bf16 h = (__bf16)x[r];
-      o.hi[r] = h;
-      o.lo[r] = (__bf16)(x[r] - (float)h);
-    }
-    return o;
-  } else {
-    return make_operand<PREC>(x, 1.f);
-  }
-}
-
 // COUNT blocks of a chain from chunk FROM (S: upwards; P: FROM-th below kb, downwards).
 template <int PREC, int KB, int kb, bool P, int M, int T, int FROM, int COUNT>
 __device__ __forceinline__ void sym_chain(f32x16 (&Y)[kAdjPB], const uint4* wv, const Operand<PREC> (&fop)[kAdjPB][KB],
@@ -147,7 +129,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
 #pragma unroll
   for (int pb = 0; pb < kAdjPB; ++pb)
 #pragma unroll
-    for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = sym_operand<PREC>(f.F[pb][uc]);
+    for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
 
   float acc[kAdjPB][KB][8];
 #pragma unroll
@@ -287,7 +269,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
 #pragma unroll
   for (int pb = 0; pb < kAdjPB; ++pb)
 #pragma unroll
-    for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = sym_operand<PREC>(f.F[pb][uc]);
+    for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
   float acc[kAdjPB][KB][8];
 #pragma unroll
   for (int pb = 0; pb < kAdjPB; ++pb)
