@@ -22,8 +22,7 @@ namespace ps {
 // hold a candidate tuple.
 // ---------------------------------------------------------------------------
 constexpr int kJThreads = 64 * kJWaves;
-static_assert(kSlots == kSlotsHost && kSlots4 == kSlots4Host && kSlots56 == kSlots56Host && kSlots6 == kSlots6Host &&
-                  kSlotsMax == kSlotsMaxHost && 2 * kSlots56 <= kSlotsMax && kMaxBlk == kMaxBlkHost &&
+static_assert(kSlots == kSlotsHost && kSlots4 == kSlots4Host && kSlotsMax == kSlotsMaxHost && kMaxBlk == kMaxBlkHost &&
                   kCtrWaves == kCtrWavesHost,
               "host and device tile tables agree");
 

@@ -1,5 +1,4 @@
-// Tile contraction kernel template (orders 2 to 6); instantiated by
-// contract_tiles_lo.hip and contract_tiles_hi.hip.
+// Tile contraction kernel template (orders 2 to 4); instantiated by contract_tiles_lo.hip.
 #pragma once
 
 #include "mfma_ops.h"
@@ -7,7 +6,7 @@
 namespace ps {
 
 template <int ORDER>
-constexpr int slots_for() { return ORDER == 2 ? 4 : ORDER == 3 ? kSlots : ORDER == 4 ? kSlots4 : ORDER == 5 ? kSlots56 : kSlots6; }
+constexpr int slots_for() { return ORDER == 2 ? 4 : ORDER == 3 ? kSlots : kSlots4; }
 
 constexpr int kMaxPairBlocks = kMaxPairBlocksHost;
 
@@ -19,14 +18,10 @@ constexpr int kMaxPairBlocks = kMaxPairBlocksHost;
 template <int PREC, int ORDER, int MB, bool PLDS = false>
 __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
   static_assert(!PLDS || (ORDER == 4 && PREC == kFP16), "shared pair operands: order 4, split FP16");
-  // FP16 up to order 4 forms pair products from the operand words alone; the other
-  // precisions, and every precision at orders 5 and 6, form their row products from
+  // FP16 forms pair products from the operand words alone; the other precisions from
   // float32 rows staged in `stage`
-  constexpr bool kFloatStage = PREC != kFP16 || ORDER >= 5;
-  // FP16 needs the per-shell power-of-two scaling for its range; at orders 5 and 6 every
-  // precision takes it, since unscaled products of five or six shell values summed over
-  // the grid overflow float32 (they reach 1e45 at 256^3)
-  constexpr bool kScaled = PREC == kFP16 || ORDER >= 5;
+  constexpr bool kFloatStage = PREC != kFP16;
+  constexpr bool kScaled = PREC == kFP16;   // the per-shell power-of-two scaling, for its range
   constexpr int kStageFloats = kFloatStage ? (MB * 16 + 1) * kRowStride : 4;
   __shared__ __attribute__((aligned(16))) float stage[2][kStageFloats];
   // [buffer][K-step][shell block][lane]; block MB stays zero (padding pairs)
@@ -60,7 +55,7 @@ __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
       if (rr >= p.n_shells) stage[buf][i % ((nrows + 1) * kRowStride)] = 0.f;
     }
   }
-  for (int i = tid; ORDER <= 4 && i < 4 * (MB + 1) * 64; i += kCtrThreads) {
+  for (int i = tid; i < 4 * (MB + 1) * 64; i += kCtrThreads) {
     const int bh = i / ((MB + 1) * 64), kb = (i / 64) % (MB + 1), ln = i % 64;
     if (kb * 16 + (ln & 15) >= p.n_shells) {
       opHi[bh >> 1][bh & 1][kb][op_slot(ln)] = make_uint4(0, 0, 0, 0);
@@ -94,9 +89,7 @@ __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
       v = make_float4(v.x * sc, v.y * sc, v.z * sc, v.w * sc);
     }
     if constexpr (kFloatStage) *reinterpret_cast<float4*>(&stage[buf][row * kRowStride + col]) = v;
-    if constexpr (ORDER >= 5) {
-      // every operand is formed from the float rows
-    } else if constexpr (PREC == kFP32) {
+    if constexpr (PREC == kFP32) {
       const uint4 w = make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
                                  __float_as_uint(v.w));
       if (half) opLo[buf][h][kb][ln] = w; else opHi[buf][h][kb][ln] = w;
@@ -122,9 +115,8 @@ __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
   // Slot state for the whole chunk.  Uniform byte per slot (4 slots per word, in
   // SGPRs): bits 0-2 B shell block, 3-5 A shell block (order 2), 6 = form A here,
   // 7 = empty.  Per-lane shells of the lane's pair rows: order 3 packs (u, v) of
-  // two slots per word, order 4 packs (u_A, v_A, u_B, v_B) of one slot per word;
-  // orders 5 and 6 use two words per slot, the A row's shells then the B row's.
-  constexpr int NLW = ORDER == 4 ? NS : ORDER >= 5 ? 2 * NS : (NS + 1) / 2;
+  // two slots per word, order 4 packs (u_A, v_A, u_B, v_B) of one slot per word.
+  constexpr int NLW = ORDER == 4 ? NS : (NS + 1) / 2;
   const int* uni = p.slot_uni + ((size_t)group * kCtrWaves + wave) * (kSlotsMax / 4);
   int un[(NS + 3) / 4];
 #pragma unroll
@@ -190,12 +182,6 @@ __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
           const int bb = blk[s] >> 16;
           const Operand<PREC> Bp = op_from_words<PREC>(pair_word(h, bb, 0), pair_word(h, bb, 1));
           mma<PREC>(acc[s], A, Bp);
-          continue;
-        }
-        if constexpr (ORDER >= 5) {
-          if (info & 0x40) A = form_rows<PREC, ORDER == 6 ? 3 : 2>(S + 32 * h, lv[2 * s], g);
-          const Operand<PREC> Bop = form_rows<PREC, 3>(S + 32 * h, lv[2 * s + 1], g);
-          mma<PREC>(acc[s], A, Bop);
           continue;
         }
         if (ORDER == 2) {

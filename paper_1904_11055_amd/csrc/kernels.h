@@ -52,7 +52,9 @@ struct CtrParams {
   int ksteps;
   int n_chunks;
   int n_pair_blocks;       // order 4, FP16: pair operands formed once per K-step in LDS (0: per slot)
-  const int* grp_blk;      // or null: [n_groups][kMaxPairBlocksHost] the group's own pair blocks (global ids)
+  const int* a_rows;       // orders 5 and 6: the A rows, staged row offsets of their shells (10 bits each)
+  const int* grp_blk;      // or null: [n_groups][kMaxPairBlocksHost] the group's own pair blocks (global ids);
+                           // orders 5 and 6: [n_groups][kHiABlocks] its A blocks
   const int* grp_nblk;     // [n_groups]: how many (then slot_blk holds indices into that list)
 };
 // Order 4, split FP16: pair blocks that fit the workgroup's LDS as shared operands
@@ -61,12 +63,16 @@ constexpr int kMaxPairBlocksHost = 28;
 constexpr int kCtrWavesHost = 16;
 constexpr int kSlotsHost = 14;
 constexpr int kSlots4Host = 10;
-constexpr int kSlots56Host = 8;
-constexpr int kSlots6Host = 7;
+// Orders 5 and 6 (contract_tiles_hi.hip): waves of a workgroup, tiles per wave, and A row
+// blocks of a tile group (formed in LDS; 4 KB each for the stage's two halves).
+constexpr int kHiWaves = 8;
+constexpr int kHiSlots = 14;
+constexpr int kHiABlocks = 11;
 constexpr int kMaxShells56 = 32;    // orders 5 and 6: shells per plan (row tables stay small)
 constexpr int kSlots2Host = 4;
 constexpr int kSlotsMaxHost = 16;   // per-wave stride of the slot tables
 constexpr int kStagePtsHost = 64;
+constexpr int kRowStrideHost = 68;   // floats per staged float32 row
 constexpr int kMaxBlkHost = 4;       // the shell-block aligned order-3 kernel (<= 64 shells)
 constexpr int kMaxTileBlkHost = 8;   // the tile kernel, orders 2 to 4 (<= 128 shells)
 constexpr int kAdjPtsHost = 512;   // grid points per adjoint workgroup

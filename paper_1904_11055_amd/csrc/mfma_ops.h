@@ -31,8 +31,6 @@ constexpr int kCtrWaves = 16;
 constexpr int kCtrThreads = 64 * kCtrWaves;
 constexpr int kSlots = 14;       // tiles per wave (order 3)
 constexpr int kSlots4 = 10;      // tiles per wave (order 4: B rows formed too)
-constexpr int kSlots56 = 8;      // tiles per wave (order 5: triple rows formed)
-constexpr int kSlots6 = 7;       // tiles per wave (order 6: triples on both sides; 8 would spill)
 constexpr int kSlotsMax = 16;    // stride of the per-wave slot tables
 constexpr int kKStep = 64;       // grid points per LDS stage (two MFMA K-steps)
 constexpr int kRowStride = 68;   // floats per staged field row (64 + 4 pad)
@@ -149,6 +147,17 @@ __device__ __forceinline__ Operand<PREC> op_from_words(uint4 h, uint4 l) {
   return o;
 }
 
+template <int PREC>
+__device__ __forceinline__ void op_to_words(const Operand<PREC>& o, uint4& h, uint4& l) {
+  if constexpr (PREC == kFP32) {
+    h = make_uint4(__float_as_uint(o.v[0]), __float_as_uint(o.v[1]), __float_as_uint(o.v[2]), __float_as_uint(o.v[3]));
+    l = make_uint4(__float_as_uint(o.v[4]), __float_as_uint(o.v[5]), __float_as_uint(o.v[6]), __float_as_uint(o.v[7]));
+  } else {
+    h = __builtin_bit_cast(uint4, o.hi);
+    l = __builtin_bit_cast(uint4, o.lo);
+  }
+}
+
 // Split four consecutive values of one operand lane into 8-byte hi and lo words.
 template <int PREC>
 __device__ __forceinline__ void split4(float4 v, float scale, uint2& hi, uint2& lo) {
@@ -188,23 +197,6 @@ __device__ __forceinline__ Operand<PREC> form_pair(const float* S, int uv, int g
 #pragma unroll
   for (int r = 0; r < 8; ++r) x[r] *= y[r];
   return make_operand<PREC>(x, 1.f);
-}
-
-// Product of NF staged shell rows (shell indices in the bytes of w), split for the
-// matrix cores.  In FP16 a triple of scaled values can reach 2^21, beyond the
-// format's range, so it enters the split scaled by 2^-kTripleShift (removed in FP64
-// with the other scale factors).
-template <int PREC, int NF>
-__device__ __forceinline__ Operand<PREC> form_rows(const float* S, int w, int g) {
-  float x[8], y[8];
-  load_row8(S + (w & 0xff) * kRowStride, g, x);
-#pragma unroll
-  for (int f = 1; f < NF; ++f) {
-    load_row8(S + ((w >> (8 * f)) & 0xff) * kRowStride, g, y);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] *= y[r];
-  }
-  return make_operand<PREC>(x, NF == 3 ? 1.0f / (1 << kTripleShift) : 1.0f);
 }
 
 // FP16 pair product straight from the split operand words of its two shell rows,

@@ -119,7 +119,8 @@ struct polyspec_plan_s {
   // order 4 with more pair blocks than one workgroup's LDS holds: each tile group's own
   // pair blocks (global ids, kMaxPairBlocksHost per group) and their count
   bool pair_groups = false;
-  DevBuf grp_blk_d, grp_nblk_d;
+  DevBuf grp_blk_d, grp_nblk_d;   // orders 5 and 6: the A blocks of each tile group
+  DevBuf a_rows_d;                // orders 5 and 6: staged row offsets of the A rows
   DevBuf closing_of_ent_d, closing_of_ent_j_d;   // streamed plans: tile entry -> closing tuple (or -1)
   // workspace carving
   DevBuf own_ws;
@@ -443,6 +444,97 @@ void build_triples(const polyspec_plan_s* p, bool by_largest, std::vector<int>* 
   while (rows->size() % 16) rows->push_back(zrow | (zrow << 8) | (zrow << 16));
 }
 
+// Orders 5 and 6: tile groups over ranges of kHiABlocks A blocks (formed once per stage in
+// LDS), each with up to kHiWaves x kHiSlots tiles; the tiles of one B block go to one wave
+// (a unit, cut where a wave has no room), which forms the block once.  A formation costs
+// about four tiles.
+polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& tlist, const std::vector<int>& arows,
+                                const std::vector<int>& brows) {
+  const int S = ps::kSlotsMaxHost, W = ps::kHiWaves, cap = ps::kHiSlots;
+  std::map<std::pair<int, int>, std::vector<int>> unit_of;   // (A range, B block) -> tiles
+  for (size_t t = 0; t < tlist.size(); ++t) unit_of[{tlist[t].a / ps::kHiABlocks, tlist[t].b}].push_back((int)t);
+  struct Wave {
+    std::vector<std::vector<int>> units;
+    int tiles = 0;
+    double load = 0;
+  };
+  struct Group {
+    int range;
+    std::vector<Wave> waves;
+  };
+  std::vector<Group> groups;
+  std::map<int, std::vector<std::vector<int>>> by_range;
+  for (const auto& kv : unit_of)
+    for (size_t f = 0; f < kv.second.size(); f += cap)
+      by_range[kv.first.first].push_back({kv.second.begin() + f,
+                                          kv.second.begin() + std::min(kv.second.size(), f + (size_t)cap)});
+  for (auto& kv : by_range) {
+    std::stable_sort(kv.second.begin(), kv.second.end(),
+                     [](const std::vector<int>& x, const std::vector<int>& y) { return x.size() > y.size(); });
+    size_t total = 0;
+    for (const auto& u : kv.second) total += u.size();
+    const size_t first = groups.size();
+    for (size_t k = 0; k < (total + (size_t)W * cap - 1) / ((size_t)W * cap); ++k)
+      groups.push_back({kv.first, std::vector<Wave>(W)});
+    for (const auto& u : kv.second) {
+      Wave* best = nullptr;
+      for (size_t k = first; k < groups.size(); ++k)
+        for (Wave& w : groups[k].waves)
+          if (w.tiles + (int)u.size() <= cap && (!best || w.load < best->load)) best = &w;
+      if (!best) {
+        groups.push_back({kv.first, std::vector<Wave>(W)});
+        best = &groups.back().waves[0];
+      }
+      best->units.push_back(u);
+      best->tiles += (int)u.size();
+      best->load += 4.0 + (double)u.size();
+    }
+  }
+  p->n_groups = (int)groups.size();
+  // staged row offset of a shell in units of 16 bytes, 10 bits per row of the product
+  auto row_word = [](int shells, int fields) {
+    int w = 0;
+    for (int f = 0; f < fields; ++f) w |= ((shells >> (8 * f)) & 0xff) * (ps::kRowStrideHost / 4) << (10 * f);
+    return w;
+  };
+  std::vector<int> a_rows(arows.size());
+  for (size_t i = 0; i < arows.size(); ++i) a_rows[i] = row_word(arows[i], p->order == 6 ? 3 : 2);
+  std::vector<int> uni((size_t)p->n_groups * W * (S / 4), 0), lanew((size_t)p->n_groups * W * 16 * S, 0);
+  std::vector<int> slot_tile((size_t)p->n_groups * W * S, -1);
+  std::vector<int> grp_blk((size_t)p->n_groups * ps::kHiABlocks, 0), grp_nblk(p->n_groups, 0);
+  for (int gi = 0; gi < p->n_groups; ++gi) {
+    std::vector<int> blocks;
+    for (const Wave& w : groups[gi].waves)
+      for (const auto& u : w.units)
+        for (int t : u) blocks.push_back(tlist[t].a);
+    std::sort(blocks.begin(), blocks.end());
+    blocks.erase(std::unique(blocks.begin(), blocks.end()), blocks.end());
+    grp_nblk[gi] = (int)blocks.size();
+    std::copy(blocks.begin(), blocks.end(), grp_blk.begin() + (size_t)gi * ps::kHiABlocks);
+    for (int w = 0; w < W; ++w) {
+      const size_t gw = (size_t)gi * W + w;
+      int s = 0;
+      for (const auto& u : groups[gi].waves[w].units) {
+        for (size_t k = 0; k < u.size(); ++k, ++s) {
+          const TileKey key = tlist[u[k]];
+          const int la = (int)(std::lower_bound(blocks.begin(), blocks.end(), key.a) - blocks.begin());
+          uni[gw * (S / 4) + s / 4] |= (la | (k == 0 ? 0x40 : 0)) << (8 * (s % 4));
+          slot_tile[gw * S + s] = u[k];
+          for (int r = 0; r < 16; ++r) lanew[(gw * 16 + r) * S + s] = row_word(brows[16 * key.b + r], 3);
+        }
+      }
+      for (; s < S; ++s) uni[gw * (S / 4) + s / 4] |= 0x80 << (8 * (s % 4));
+    }
+  }
+  PS_TRY(upload(p, &p->slots_d, uni));
+  PS_TRY(upload(p, &p->slot_lane_d, lanew));
+  PS_TRY(upload(p, &p->slot_tile_d, slot_tile));
+  PS_TRY(upload(p, &p->a_rows_d, a_rows));
+  PS_TRY(upload(p, &p->grp_blk_d, grp_blk));
+  PS_TRY(upload(p, &p->grp_nblk_d, grp_nblk));
+  return POLYSPEC_OK;
+}
+
 polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   std::vector<int> pidx;
   build_pairs(p, &pidx);
@@ -494,12 +586,11 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
     const int t = tiles[TileKey{loc[c][0], loc[c][1]}];
     (*ent_of_cand)[c] = t * 256 + tile_entry(loc[c][2], loc[c][3]);
   }
+  if (n >= 5) return pack_high_order(p, tlist, arows, brows);
   // units: runs of tiles sharing the A block, cut into pieces that fit one wave
   const int cap = n == 2   ? ps::kSlots2Host
                   : n == 3 ? ps::kSlotsHost
-                  : n == 4 ? ps::kSlots4Host
-                  : n == 5 ? ps::kSlots56Host
-                           : ps::kSlots6Host;
+                           : ps::kSlots4Host;
   std::vector<std::pair<int, int>> units;  // [first tile, count]
   for (int t = 0; t < id;) {
     int u = t;
@@ -576,7 +667,7 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
         best = &groups.back()[0];
       }
       for (int k = 0; k < cnt; ++k) best->tiles.push_back(units[ui].first + k);
-      best->load += 1.0 + cnt * (n >= 5 ? 3.0 : n == 4 ? 2.0 : 1.0);   // one A formation + the tiles
+      best->load += 1.0 + cnt * (n == 4 ? 2.0 : 1.0);   // one A formation + the tiles
     }
   }
   p->n_groups = (int)groups.size();
@@ -607,7 +698,7 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
           const TileKey k = tlist[tl[s]];
           const int form = k.a != prev_a ? 1 : 0;
           prev_a = k.a;
-          info = (n >= 4 ? 0 : (k.b & 7)) | (n == 2 ? (k.a & 7) << 3 : 0) | (form << 6);
+          info = (n == 4 ? 0 : (k.b & 7)) | (n == 2 ? (k.a & 7) << 3 : 0) | (form << 6);
           slot_tile[gw * S + s] = tl[s];
           if (p->pair_groups) {   // the group's local block indices
             const int* gb = &grp_blk[(size_t)gi * lmax];
@@ -620,10 +711,6 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
             int* row_words = &lanew[(gw * 16 + r) * S];
             if (n == 3) row_words[s / 2] |= uv8(16 * k.a + r) << (16 * (s % 2));
             if (n == 4) row_words[s] = uv8(16 * k.a + r) | (uv8(16 * k.b + r) << 16);
-            if (n >= 5) {
-              row_words[2 * s] = arows[16 * k.a + r];
-              row_words[2 * s + 1] = brows[16 * k.b + r];
-            }
           }
         }
         uni[gw * (S / 4) + s / 4] |= info << (8 * (s % 4));
@@ -1052,7 +1139,7 @@ void release(polyspec_plan_s* p) {
   p->ev_pool.clear();
   DevBuf* bufs[] = {&p->tw32, &p->shell_q, &p->qmax_d, &p->pairs_d, &p->slots_d, &p->slot_lane_d, &p->slot_tile_d, &p->slot_blk_d, &p->ent_d,
                     &p->bins_d, &p->fnorm_d, &p->lookup_d, &p->wmask_d, &p->pmask_d, &p->flag_d, &p->jtile_d, &p->jmask_d,
-                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->grp_blk_d, &p->grp_nblk_d,
+                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->grp_blk_d, &p->grp_nblk_d, &p->a_rows_d,
                     &p->own_ws};
   for (DevBuf* b : bufs) dev_free(b);
 }
@@ -1281,8 +1368,10 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     const int npb = p->n_pairs_padded / 16;
     const bool plds = p->order == 4 && p->prec == POLYSPEC_SPLIT_FP16 && p->n_blk <= 4;
     cp.n_pair_blocks = !plds ? 0 : p->pair_groups ? ps::kMaxPairBlocksHost : npb;
-    cp.grp_blk = plds && p->pair_groups ? (const int*)p->grp_blk_d.p : nullptr;
-    cp.grp_nblk = plds && p->pair_groups ? (const int*)p->grp_nblk_d.p : nullptr;
+    const bool grp = p->order >= 5 || (plds && p->pair_groups);
+    cp.grp_blk = grp ? (const int*)p->grp_blk_d.p : nullptr;
+    cp.grp_nblk = grp ? (const int*)p->grp_nblk_d.p : nullptr;
+    cp.a_rows = (const int*)p->a_rows_d.p;
     PS_TIMED(p, POLYSPEC_PH_CONTRACT, ps::launch_contract(p->prec, p->order, cp, p->n_groups, p->batch, st));
     *n_ent = (long long)p->n_tiles * 256;
     n_chunks = p->n_chunks;
