@@ -40,6 +40,18 @@ struct FftCfg<double> {
   static constexpr int kRowElems = 2048;
 };
 
+// Pencils per block of a column pass over `elems` complex values: at most 16 (runs of 128
+// bytes; more only pad the last block of a row, whose columns the ball does not fill), but
+// enough that 256 threads have a radix-8 butterfly each.  Against elems / N pencils
+// everywhere: shell pass 2 at 128^3 x 192 fields of 25 columns 0.50 -> 0.23 ms, 256^3 / 40
+// shells 0.86 -> 0.67, 64^3 / 16 shells 22 -> 10 us.
+template <typename T>
+constexpr int col_pencils(int N, int elems) {
+  if (sizeof(T) == 8) return elems / N;
+  const int p = elems / N < 16 ? elems / N : 16, lo = 8 * kFftThreads / N;
+  return p > lo ? p : lo;
+}
+
 __device__ __forceinline__ int freq_of(int n, int N) { return n < N / 2 ? n : n - N; }
 
 // ---------------------------------------------------------------------------
@@ -57,7 +69,7 @@ __global__ __launch_bounds__(kFftThreads) void c2r_p1(const cplx<float>* __restr
                                                       const int* __restrict__ qmax,
                                                       cplx<T>* __restrict__ H1,
                                                       const cplx<T>* __restrict__ tw, Geom g) {
-  constexpr int P = FftCfg<T>::kElems / N;
+  constexpr int P = col_pencils<T>(N, FftCfg<T>::kElems);
   constexpr int NS = pencil_stride<N>();
   __shared__ cplx<T> buf[P * NS];
   __shared__ cplx<T> stw[stage_tw_size<N>()];
@@ -131,7 +143,7 @@ __global__ __launch_bounds__(kFftThreads) void c2r_p2(const cplx<T>* __restrict_
                                                       const int* __restrict__ qmax,
                                                       cplx<T>* __restrict__ H2,
                                                       const cplx<T>* __restrict__ tw, Geom g) {
-  constexpr int P = FftCfg<T>::kColElems / N;
+  constexpr int P = col_pencils<T>(N, FftCfg<T>::kColElems);
   constexpr int NS = pencil_stride<N>();
   __shared__ cplx<T> buf[P * NS];
   __shared__ cplx<T> stw[stage_tw_size<N>()];
@@ -387,7 +399,7 @@ __global__ __launch_bounds__(kFftThreads) void r2c_q2(const cplx<float>* __restr
                                                       cplx<float>* __restrict__ H1,
                                                       const cplx<float>* __restrict__ tw, Geom g, int reps) {
   using T = float;
-  constexpr int P = FftCfg<T>::kElems / N;
+  constexpr int P = col_pencils<T>(N, FftCfg<T>::kElems);
   constexpr int NS = pencil_stride<N>();
   __shared__ cplx<T> buf[P * NS];
   __shared__ cplx<T> stw[stage_tw_size<N>()];
@@ -431,7 +443,7 @@ __global__ __launch_bounds__(kFftThreads) void r2c_q1(const cplx<float>* __restr
                                                       cplx<float>* __restrict__ box,
                                                       const cplx<float>* __restrict__ tw, Geom g) {
   using T = float;
-  constexpr int P = FftCfg<T>::kElems / N;
+  constexpr int P = col_pencils<T>(N, FftCfg<T>::kElems);
   constexpr int NS = pencil_stride<N>();
   __shared__ cplx<T> buf[P * NS];
   __shared__ cplx<T> stw[stage_tw_size<N>()];
@@ -524,9 +536,6 @@ __global__ void half_spectrum_from_box(const cplx<float>* __restrict__ box, cplx
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
-template <typename T>
-int fft_pencils_per_block(int N) { return FftCfg<T>::kElems / N; }
-
 // Work items per block for the looping passes: a power of two up to `cap` that
 // divides the items and keeps at least 16K blocks in the launch (the per-block setup
 // -- stage twiddles in LDS, block start -- is then paid once per `reps` items).
@@ -542,7 +551,7 @@ int loop_reps(size_t items, int nz, int cap = 16) {
 template <typename T, bool UNIT>
 hipError_t launch_c2r_p1(const cplx<float>* box, const int16_t* sq, const int* qmax, cplx<T>* H1,
                          const cplx<T>* tw, Geom g, int nz, hipStream_t st) {
-  const int P = FftCfg<T>::kElems / g.N;
+  const int P = col_pencils<T>(g.N, FftCfg<T>::kElems);
   dim3 grid((g.B0 + P - 1) / P, g.B2, nz);
   switch (g.N) {
 #define CASE(n) \
@@ -557,7 +566,7 @@ hipError_t launch_c2r_p1(const cplx<float>* box, const int16_t* sq, const int* q
 template <typename T>
 hipError_t launch_c2r_p2(const cplx<T>* H1, const int* qmax, cplx<T>* H2, const cplx<T>* tw, Geom g, int nz,
                          hipStream_t st) {
-  const int P = FftCfg<T>::kColElems / g.N;
+  const int P = col_pencils<T>(g.N, FftCfg<T>::kColElems);
   if (g.S1 < 1 || g.x1_0 < 0 || g.x1_0 + g.S1 > g.N) return hipErrorInvalidValue;
   dim3 grid((g.B2 + P - 1) / P, g.S1, nz);
   switch (g.N) {
@@ -628,7 +637,7 @@ hipError_t launch_r2c_q3(const float* in, cplx<float>* H2, const cplx<float>* tw
 
 hipError_t launch_r2c_q2(const cplx<float>* H2, cplx<float>* H1, const cplx<float>* tw, Geom g, int nz,
                          hipStream_t st) {
-  const int P = FftCfg<float>::kElems / g.N;
+  const int P = col_pencils<float>(g.N, FftCfg<float>::kElems);
   if (g.S1 < 1 || g.x1_0 < 0 || g.x1_0 + g.S1 > g.N) return hipErrorInvalidValue;
   const int cb = (g.B2 + P - 1) / P;
   const int reps = loop_reps(g.S1, cb * nz);
@@ -645,7 +654,7 @@ hipError_t launch_r2c_q2(const cplx<float>* H2, cplx<float>* H1, const cplx<floa
 template <bool MASK>
 hipError_t launch_r2c_q1(const cplx<float>* H1, const int16_t* sq, const int* qmax, cplx<float>* box,
                          const cplx<float>* tw, Geom g, int nz, hipStream_t st) {
-  const int P = FftCfg<float>::kElems / g.N;
+  const int P = col_pencils<float>(g.N, FftCfg<float>::kElems);
   dim3 grid((g.B0 + P - 1) / P, g.B2, nz);
   switch (g.N) {
 #define CASE(n) \

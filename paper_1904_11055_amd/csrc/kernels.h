@@ -9,8 +9,6 @@
 namespace ps {
 
 // fft.hip
-template <typename T>
-int fft_pencils_per_block(int N);
 template <typename T, bool UNIT>
 hipError_t launch_c2r_p1(const cplx<float>* box, const int16_t* shell_of_q, const int* qmax, cplx<T>* H1,
                          const cplx<T>* tw, Geom g, int nz, hipStream_t st);
