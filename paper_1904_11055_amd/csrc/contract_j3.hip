@@ -3,7 +3,7 @@
 namespace ps {
 
 // ---------------------------------------------------------------------------
-// Order 3, pair blocks aligned to shell blocks (FP16 split).
+// Order 3, products aligned to shell blocks (up to 64 shells, every precision).
 //   S[i, j, k] = sum_x d_i d_j d_k, i <= j <= k, by the 16-shell block jb of the middle shell.
 // Every 16 x 16 tile is a product operand (16 rows d_p d_j) times the plain operand of a
 // shell block held in registers.  What fixes the rows of the product operand:
@@ -36,11 +36,20 @@ static_assert(kSlots == kSlotsHost && kSlots4 == kSlots4Host && kSlotsMax == kSl
 // 34.7 with the next step's fields split in the middle of the step instead of before its
 // barrier.  What is left: without staging 28 ms, without forming products 29.7, the matrix
 // products alone 20.  128^3 x 8, 24 shells: 1.99 -> 0.98 ms.
-template <int NBLK, bool ALL>
+//
+// FP16 forms the products from the split words; FP32 and BF16 from float32 values, which
+// BF16 splits afterwards, as the pair tiles of contract_tiles do (the plan chooses between
+// the two).  512^3, 64 shells: BF16 63.2 -> 40.8 ms, FP32 119 -> 99.7; 256^3, 53 shells:
+// BF16 5.99 -> 5.17.
+template <int PREC, int NBLK, bool ALL>
 __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
-  constexpr int PREC = kFP16;
-  __shared__ uint4 opHi[2][2][kMaxBlk][64];   // [buffer][K-step][shell block][lane]
+  // [buffer][K-step][shell block][lane]: the operand's 16-byte words, FP16 hi and lo, else
+  // the float32 values 0..3 and 4..7; BF16 keeps the split words beside them
+  __shared__ uint4 opHi[2][2][kMaxBlk][64];
   __shared__ uint4 opLo[2][2][kMaxBlk][64];
+  constexpr int kSp = PREC == kBF16 ? kMaxBlk * 64 : 1;
+  __shared__ uint4 spHi[2][2][kSp];
+  __shared__ uint4 spLo[2][2][kSp];
   __shared__ float lds_scale[kMaxBlk * 16];
 
   const int tid = threadIdx.x;
@@ -51,12 +60,14 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
   const int b = blockIdx.z;
 
   for (int i = tid; i < kMaxBlk * 16; i += kJThreads)
-    lds_scale[i] = i < p.n_shells ? ldexpf(1.0f, shell_scale_exp(p.absmax, b * p.n_shells + i)) : 0.f;
+    lds_scale[i] = PREC != kFP16 ? 1.f : i < p.n_shells ? ldexpf(1.0f, shell_scale_exp(p.absmax, b * p.n_shells + i)) : 0.f;
   for (int i = tid; i < 4 * kMaxBlk * 64; i += kJThreads) {
     const int bh = i / (kMaxBlk * 64), kb = (i / 64) % kMaxBlk, ln = i % 64;
     if (kb * 16 + (ln & 15) >= p.n_shells) {
       opHi[bh >> 1][bh & 1][kb][op_slot(ln)] = make_uint4(0, 0, 0, 0);
       opLo[bh >> 1][bh & 1][kb][op_slot(ln)] = make_uint4(0, 0, 0, 0);
+      if constexpr (PREC == kBF16)
+        spHi[bh >> 1][bh & 1][kb * 64 + op_slot(ln)] = spLo[bh >> 1][bh & 1][kb * 64 + op_slot(ln)] = make_uint4(0, 0, 0, 0);
     }
   }
   __syncthreads();
@@ -83,13 +94,16 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
   auto stage_store = [&](int buf, int f) {
     const int idx = tid + f * kJThreads, row = idx >> 4, col = (idx & 15) * 4;
     const float sc = st_scale[f];
-    const float4 v = st_on[f] ? make_float4(pre[f].x * sc, pre[f].y * sc, pre[f].z * sc, pre[f].w * sc)
-                              : make_float4(0.f, 0.f, 0.f, 0.f);
-    uint2 hi, lo;
-    split4<PREC>(v, 1.f, hi, lo);
+    float4 v = st_on[f] ? pre[f] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int h = col >> 5, kb = row >> 4, ln = op_slot((((col & 31) >> 3) << 4) | (row & 15)), half = (col >> 2) & 1;
-    reinterpret_cast<uint2*>(&opHi[buf][h][kb][ln])[half] = hi;
-    reinterpret_cast<uint2*>(&opLo[buf][h][kb][ln])[half] = lo;
+    if constexpr (PREC == kFP16) v = make_float4(v.x * sc, v.y * sc, v.z * sc, v.w * sc);
+    else *reinterpret_cast<float4*>(half ? &opLo[buf][h][kb][ln] : &opHi[buf][h][kb][ln]) = v;
+    if constexpr (PREC != kFP32) {
+      uint2 hi, lo;
+      split4<PREC>(v, 1.f, hi, lo);
+      reinterpret_cast<uint2*>(PREC == kFP16 ? &opHi[buf][h][kb][ln] : &spHi[buf][h][(kb * 64 + ln) % kSp])[half] = hi;
+      reinterpret_cast<uint2*>(PREC == kFP16 ? &opLo[buf][h][kb][ln] : &spLo[buf][h][(kb * 64 + ln) % kSp])[half] = lo;
+    }
   };
   stage_load(0);
 #pragma unroll
@@ -124,24 +138,50 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
       mm = __builtin_amdgcn_readfirstlane(mm);
       const uint4* hi = &opHi[cur][h][0][0];
       const uint4* lo = &opLo[cur][h][0][0];
-      auto words = [&](int i) { return op_from_words<PREC>(hi[i], lo[i]); };
+      constexpr int WP = PREC == kFP16 ? kFP16 : kFP32;           // what a product is formed from
+      auto words = [&](int i) { return op_from_words<WP>(hi[i], lo[i]); };
+      auto product = [&](const Operand<WP>& x, const Operand<WP>& y) {
+        if constexpr (PREC == kFP16) {
+          return pair_f16(x, y);
+        } else {
+          float z[8];
+#pragma unroll
+          for (int r = 0; r < 8; ++r) z[r] = x.v[r] * y.v[r];
+          return make_operand<PREC>(z, 1.f);
+        }
+      };
       Operand<PREC> Bop[NBLK];
 #pragma unroll
-      for (int kb = 0; kb < NBLK; ++kb) Bop[kb] = words(64 * kb + my_slot);
+      for (int kb = 0; kb < NBLK; ++kb) {
+        if constexpr (PREC == kBF16)
+          Bop[kb] = op_from_words<PREC>(spHi[cur][h][64 * kb + my_slot], spLo[cur][h][64 * kb + my_slot]);
+        else
+          Bop[kb] = words(64 * kb + my_slot);
+      }
+      // a plain block as a factor of a product
+      auto plain = [&](auto kc) {
+        if constexpr (PREC == kBF16) return words(64 * decltype(kc)::value + my_slot);
+        else return Bop[decltype(kc)::value];
+      };
       // Slots s0 .. s0 + CNT - 1: the product operand times the blocks x0, x0 + 1, ... of the
-      // plan, the three products of the split in turn, so that none waits for the one before
-      // it.
+      // plan, the products of the split in turn, so that none waits for the one before it.
       auto tiles = [&](auto s0c, auto cntc, auto x0c, auto&& form) {
         constexpr int s0 = decltype(s0c)::value, x0 = decltype(x0c)::value;
         constexpr int CNT = decltype(cntc)::value < NBLK - x0 ? decltype(cntc)::value : NBLK - x0;
         if constexpr (CNT > 0) {
           if (!ALL && (mm & (((1u << CNT) - 1) << s0)) == 0) return;
           const Operand<PREC> A = form();
-          static_for<3>([&](auto term) {
+          if constexpr (PREC == kFP32 && !ALL) {   // a tile is 256 cycles of products: worth a branch
             static_for<CNT>([&](auto c) {
-              mma_term<decltype(term)::value>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
+              if ((mm >> (s0 + decltype(c)::value)) & 1) mma<PREC>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
             });
-          });
+          } else {
+            static_for<PREC == kFP32 ? 8 : 3>([&](auto term) {
+              static_for<CNT>([&](auto c) {
+                mma_term<PREC, decltype(term)::value>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
+              });
+            });
+          }
         }
       };
       // one tile that the triangle bound empties for all but the last shell of a block
@@ -151,30 +191,30 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
           if ((mm >> s0) & 1) mma<PREC>(acc[s0], form(), Bop[x]);
       };
 #define PS_C(v) std::integral_constant<int, v>{}
-      auto diag0 = [&] { return pair_f16(words(ap), words(aj)); };
+      auto diag0 = [&] { return product(words(ap), words(aj)); };
       tiles(PS_C(kJDiag0), PS_C(2), PS_C(0), diag0);
-      tiles(PS_C(kJDiag1), PS_C(3), PS_C(1), [&] { return pair_f16(words(64 + ap), words(64 + aj)); });
+      tiles(PS_C(kJDiag1), PS_C(3), PS_C(1), [&] { return product(words(64 + ap), words(64 + aj)); });
       if constexpr (NBLK > 2)
-        tiles(PS_C(kJDiag2), PS_C(3), PS_C(0), [&] { return pair_f16(words(128 + bp), words(128 + bj)); });
+        tiles(PS_C(kJDiag2), PS_C(3), PS_C(0), [&] { return product(words(128 + bp), words(128 + bj)); });
       if constexpr (NBLK > 3)
-        tiles(PS_C(kJDiag3), PS_C(4), PS_C(0), [&] { return pair_f16(words(192 + bp), words(192 + bj)); });
+        tiles(PS_C(kJDiag3), PS_C(4), PS_C(0), [&] { return product(words(192 + bp), words(192 + bj)); });
       // the next step's fields, split under the products
       if (h == 1) stage_store(cur ^ 1, 0);
       static_for<2>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         if (h == 1 && q == 1 && kF4 == 2) stage_store(cur ^ 1, kF4 - 1);
-        tiles(PS_C(kJLow + 3 * q), PS_C(2), PS_C(1), [&] { return pair_f16(Bop[0], words(64 + uj[q])); });
+        tiles(PS_C(kJLow + 3 * q), PS_C(2), PS_C(1), [&] { return product(plain(PS_C(0)), words(64 + uj[q])); });
         if constexpr (NBLK > 3)
-          tiles(PS_C(kJHigh + 3 * q), PS_C(3), PS_C(0), [&] { return pair_f16(Bop[3], words(128 + uj[q])); });
+          tiles(PS_C(kJHigh + 3 * q), PS_C(3), PS_C(0), [&] { return product(plain(PS_C(3)), words(128 + uj[q])); });
       });
       if ((mm >> kJShared) != 0) {
-        if (wave & 1) tiles(PS_C(kJShared), PS_C(2), PS_C(2), [&] { return pair_f16(words(xp), words(xj)); });
-        else tiles(PS_C(kJShared), PS_C(2), PS_C(0), [&] { return pair_f16(words(xp), words(xj)); });
+        if (wave & 1) tiles(PS_C(kJShared), PS_C(2), PS_C(2), [&] { return product(words(xp), words(xj)); });
+        else tiles(PS_C(kJShared), PS_C(2), PS_C(0), [&] { return product(words(xp), words(xj)); });
       }
       corner(PS_C(kJDiag0 + 2), PS_C(2), diag0);
       corner(PS_C(kJDiag0 + 3), PS_C(3), diag0);
-      corner(PS_C(kJLow + 2), PS_C(3), [&] { return pair_f16(Bop[0], words(64 + uj[0])); });
-      corner(PS_C(kJLow + 5), PS_C(3), [&] { return pair_f16(Bop[0], words(64 + uj[1])); });
+      corner(PS_C(kJLow + 2), PS_C(3), [&] { return product(plain(PS_C(0)), words(64 + uj[0])); });
+      corner(PS_C(kJLow + 5), PS_C(3), [&] { return product(plain(PS_C(0)), words(64 + uj[1])); });
 #undef PS_C
     }
     __syncthreads();
@@ -190,16 +230,20 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
 }
 
 hipError_t launch_contract_j3(int prec, const CtrJParams& p, int batch, hipStream_t st) {
-  if (prec != kFP16) return hipErrorInvalidValue;
   dim3 grid(p.n_chunks, 1, batch);
-#define L(NBLK, ALL) hipLaunchKernelGGL((contract_j3<NBLK, ALL>), grid, dim3(kJThreads), 0, st, p)
-  switch (p.n_blk) {
-    case 1: L(1, false); break;
-    case 2: L(2, false); break;
-    case 3: if (p.all_used) L(3, true); else L(3, false); break;
-    case 4: if (p.all_used) L(4, true); else L(4, false); break;
-    default: return hipErrorInvalidValue;
+#define L(PREC, NBLK, ALL) hipLaunchKernelGGL((contract_j3<PREC, NBLK, ALL>), grid, dim3(kJThreads), 0, st, p)
+#define BY_BLOCKS(PREC)                                                       \
+  switch (p.n_blk) {                                                          \
+    case 1: L(PREC, 1, false); break;                                         \
+    case 2: L(PREC, 2, false); break;                                         \
+    case 3: if (p.all_used) L(PREC, 3, true); else L(PREC, 3, false); break;  \
+    case 4: if (p.all_used) L(PREC, 4, true); else L(PREC, 4, false); break;  \
+    default: return hipErrorInvalidValue;                                     \
   }
+  if (prec == kFP32) BY_BLOCKS(kFP32)
+  else if (prec == kBF16) BY_BLOCKS(kBF16)
+  else BY_BLOCKS(kFP16)
+#undef BY_BLOCKS
 #undef L
   return hipGetLastError();
 }

@@ -95,10 +95,16 @@ __device__ __forceinline__ void mma(f32x4& acc, const Operand<PREC>& a, const Op
   }
 }
 
-// One of the three products of the FP16 split: hi hi, hi lo, lo hi.
-template <int TERM>
-__device__ __forceinline__ void mma_term(f32x4& acc, const Operand<kFP16>& a, const Operand<kFP16>& b) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(TERM == 2 ? a.lo : a.hi, TERM == 1 ? b.lo : b.hi, acc, 0, 0, 0);
+// One of the matrix products of mma(): of the splits hi hi, hi lo, lo hi; of FP32 one of the
+// eight K-steps of 4.
+template <int PREC, int TERM>
+__device__ __forceinline__ void mma_term(f32x4& acc, const Operand<PREC>& a, const Operand<PREC>& b) {
+  if constexpr (PREC == kFP32)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[TERM], b.v[TERM], acc, 0, 0, 0);
+  else if constexpr (PREC == kBF16)
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(TERM == 2 ? a.lo : a.hi, TERM == 1 ? b.lo : b.hi, acc, 0, 0, 0);
+  else
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(TERM == 2 ? a.lo : a.hi, TERM == 1 ? b.lo : b.hi, acc, 0, 0, 0);
 }
 
 // Lane l of a 16x16x32 operand holds row (l % 16) at grid points 8 (l / 16) .. +7

@@ -106,10 +106,11 @@ struct polyspec_plan_s {
   int red_groups = 0, red_cpg = 0;
   int n_adj_active = 0;
   std::vector<int> pair_uv;
-  // shell-block aligned order-3 schedule (FP16 split)
+  // shell-block aligned order-3 schedule
   std::vector<int> wmask_host;     // adjoint: per v, bits 2 uc + mb of weight blocks
   std::vector<int> pmask_host;     // order-4 adjoint: per l, the pairs of partners with a weight
   bool jsched = false, j_all_used = false;
+  int j_load = 0;   // four times the largest number of its tiles on one SIMD
   int n_tiles_j = 0, ksteps_j = 0, n_chunks_j = 0;
 
   // device tables
@@ -750,6 +751,9 @@ polyspec_status build_jsched(polyspec_plan_s* p, std::vector<int>* ent_of_cand) 
       mask[w] |= 1u << s;
     }
   p->n_tiles_j = id;
+  int per_simd[4] = {};
+  for (int w = 0; w < ps::kJWaves; ++w) per_simd[w % 4] += __builtin_popcount(mask[w]);
+  p->j_load = 4 * *std::max_element(per_simd, per_simd + 4);
   // slots of each kind (the corners of contract_j3 left out), as far as the plan's blocks go
   p->j_all_used = true;
   for (int w = 0; w < ps::kJWaves; ++w) {
@@ -1321,6 +1325,19 @@ polyspec_status polyspec_shells(polyspec_plan_t p, const void* d_delta) {
   return shells_impl(p, d_delta);
 }
 
+// Whether an order-3 plan contracts by contract_j3 (products aligned to shell blocks) or by the
+// pair tiles of contract_tiles.  FP16: always.  FP32 spends its time in the matrix products
+// alone, so it takes the schedule with fewer tiles on its busiest SIMD (256^3: 40 shells, 96
+// against 84 pair tiles, 6.34 against 5.91 ms; 48 shells, 96 against 106, 6.64 against 7.76);
+// BF16 forms fewer operands the aligned way, which pays for 15% more tiles (40 shells 2.96
+// against 3.26 ms; 33 shells, 80 against 68 tiles, 2.70 against 2.39).  Plans of one shell
+// block are bound by the staging and take it always (13 shells: FP32 0.75 against 0.89 ms).
+static bool uses_j3(const polyspec_plan_s* p) {
+  if (!p->jsched) return false;
+  if (p->prec == POLYSPEC_SPLIT_FP16 || p->n_blk == 1) return true;
+  return p->j_load <= p->n_tiles * (p->prec == POLYSPEC_SPLIT_BF16 ? 1.15 : 1.0);
+}
+
 // One contraction launch over the fields in D (the whole grid or one slab) and its
 // FP64 reduction over chunks into p->red, added to what is there when `accumulate`.
 // Returns the tile entries and entry table that the gather needs.
@@ -1328,7 +1345,7 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
                                        const int** ent) {
   hipStream_t st = p->stream;
   int n_chunks;
-  if (p->jsched && p->prec == POLYSPEC_SPLIT_FP16 && p->ksteps_j % 4 == 0) {   // whole 256-point stages
+  if (uses_j3(p)) {
     ps::CtrJParams jp;
     jp.D = p->D;
     jp.absmax = p->absmax;
@@ -1642,8 +1659,7 @@ polyspec_status polyspec_issued_flops(polyspec_plan_t p, int32_t phase, double* 
   *flops = 0.0;
   if (phase == POLYSPEC_PH_CONTRACT) {
     // a 16 x 16 tile is 2 * 256 flops per grid point and product term
-    const bool aligned = p->jsched && p->prec == POLYSPEC_SPLIT_FP16 && p->ksteps_j % 4 == 0;
-    *flops = (aligned ? p->n_tiles_j : p->n_tiles) * 512.0 * terms * pts;
+    *flops = (uses_j3(p) ? p->n_tiles_j : p->n_tiles) * 512.0 * terms * pts;
   } else if (phase == POLYSPEC_PH_ADJ_GEMM && p->order == 4 && p->nb <= ps::kAdj4MaxShells) {
     // 32 x 32 x 16 products per 32 grid points.  FP16: per item (w, v) the 16-shell chunks
     // of u <= v, for each 32-row block of m with a weight (the only block up to 32

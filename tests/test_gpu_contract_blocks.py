@@ -1,4 +1,4 @@
-"""The order-3 FP16 contraction at the edges of its shell blocks: shells that fill a product
+"""The order-3 contraction by aligned products at the edges of its shell blocks: shells that fill a product
 operand alone, share one from either end, or leave it half empty, against the FP64 oracle.
 
 Tolerance: 1e-4 relative L2 over the tuples, the gate of the split-precision contraction.
@@ -21,14 +21,14 @@ def _reference(N, nb, width, aliased):
     return _CACHE[key]
 
 
-def _check(N, nb, width, aliased, all_shells):
+def _check(N, nb, width, aliased, all_shells, precision=2):
     """A plan of nb shells against the tuples of the largest plan that it shares."""
     import torch
 
     import paper_1904_11055_amd as ps
     delta, ref = _reference(N, all_shells, width, aliased)
     keep = ref["tuples"].max(axis=1) <= nb
-    plan = ps.Plan(N, 3, nb, width, precision=ps.SPLIT_FP16, flags=ps.ALLOW_ALIASING if aliased else 0, device="cuda:0")
+    plan = ps.Plan(N, 3, nb, width, precision=precision, flags=ps.ALLOW_ALIASING if aliased else 0, device="cuda:0")
     plan.shells(torch.from_numpy(delta)[None].to("cuda:0"))
     B, S = (v.cpu().numpy()[0] for v in plan.contract(raw=True))
     assert np.array_equal(plan.tuples, ref["tuples"][keep])
@@ -52,3 +52,12 @@ def test_shell_blocks(gpu, nb):
 def test_aliased(gpu, nb):
     """Aliased: every tuple closes, the corner tiles included."""
     _check(32, nb, 0.25, True, 63)
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nb", [9, 16, 40, 48, 49, 63, 64])
+def test_other_precisions(gpu, nb, precision):
+    """FP32 and BF16 on the plans that take the aligned products (one block; 48 and more), and
+    on one that chooses by precision (40)."""
+    _check(64, nb, 0.25, False, 64, precision)
