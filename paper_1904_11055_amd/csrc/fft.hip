@@ -44,7 +44,9 @@ struct FftCfg<double> {
 // bytes; more only pad the last block of a row, whose columns the ball does not fill), but
 // enough that 256 threads have a radix-8 butterfly each.  Against elems / N pencils
 // everywhere: shell pass 2 at 128^3 x 192 fields of 25 columns 0.50 -> 0.23 ms, 256^3 / 40
-// shells 0.86 -> 0.67, 64^3 / 16 shells 22 -> 10 us.
+// shells 0.86 -> 0.67, 64^3 / 16 shells 22 -> 10 us; the adjoint's q2 at 128^3 x 192 fields
+// 0.31 -> 0.23.  The inverse passes' values do not depend on the choice (fft_stage); the
+// forward ones' last bits do, so the input's transform, 2 us of a 64^3 spectrum, keeps elems / N.
 template <typename T>
 constexpr int col_pencils(int N, int elems) {
   if (sizeof(T) == 8) return elems / N;
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(kFftThreads) void c2r_p1(const cplx<float>* __restr
     buf[pp * NS + pad8(n)] = val;
   }
   __syncthreads();
-  fft_block<T, N, P, NS, +1>(buf, stw);
+  fft_block<T, N, P, NS, +1, kFftThreads, FftCfg<T>::kElems / N>(buf, stw, a0 % (FftCfg<T>::kElems / N));
   // store H1[z][x1][c][a0 + pp]
   cplx<T>* out = H1 + (size_t)z * N * g.B2 * g.B0;
 #pragma unroll
@@ -170,7 +172,7 @@ __global__ __launch_bounds__(kFftThreads) void c2r_p2(const cplx<T>* __restrict_
     buf[pp * NS + pad8(n)] = val;
   }
   __syncthreads();
-  fft_block<T, N, P, NS, +1>(buf, stw);
+  fft_block<T, N, P, NS, +1, kFftThreads, FftCfg<T>::kColElems / N>(buf, stw, c0 % (FftCfg<T>::kColElems / N));
   cplx<T>* out = H2 + (size_t)z * N * g.S1 * g.H2s;
 #pragma unroll
   for (int m = 0; m < E; ++m) {
@@ -394,12 +396,12 @@ __global__ __launch_bounds__(kFftThreads) void r2c_q3(const float* __restrict__ 
 // Q2: pencils (x1, c) for the x1 planes of the slab, transform x0 -> q0, keep
 // |q0| <= Kc; writes rows x1 of the whole H1.  grid (ceil(B2/P), S1/reps, nz): a
 // block takes `reps` consecutive planes.
-template <int N>
+template <int N, bool GRAD>
 __global__ __launch_bounds__(kFftThreads) void r2c_q2(const cplx<float>* __restrict__ H2,
                                                       cplx<float>* __restrict__ H1,
                                                       const cplx<float>* __restrict__ tw, Geom g, int reps) {
   using T = float;
-  constexpr int P = col_pencils<T>(N, FftCfg<T>::kElems);
+  constexpr int P = GRAD ? col_pencils<T>(N, FftCfg<T>::kElems) : FftCfg<T>::kElems / N;
   constexpr int NS = pencil_stride<N>();
   __shared__ cplx<T> buf[P * NS];
   __shared__ cplx<T> stw[stage_tw_size<N>()];
@@ -443,7 +445,7 @@ __global__ __launch_bounds__(kFftThreads) void r2c_q1(const cplx<float>* __restr
                                                       cplx<float>* __restrict__ box,
                                                       const cplx<float>* __restrict__ tw, Geom g) {
   using T = float;
-  constexpr int P = col_pencils<T>(N, FftCfg<T>::kElems);
+  constexpr int P = MASK ? col_pencils<T>(N, FftCfg<T>::kElems) : FftCfg<T>::kElems / N;
   constexpr int NS = pencil_stride<N>();
   __shared__ cplx<T> buf[P * NS];
   __shared__ cplx<T> stw[stage_tw_size<N>()];
@@ -635,15 +637,16 @@ hipError_t launch_r2c_q3(const float* in, cplx<float>* H2, const cplx<float>* tw
   return hipGetLastError();
 }
 
+template <bool GRAD>
 hipError_t launch_r2c_q2(const cplx<float>* H2, cplx<float>* H1, const cplx<float>* tw, Geom g, int nz,
                          hipStream_t st) {
-  const int P = col_pencils<float>(g.N, FftCfg<float>::kElems);
+  const int P = GRAD ? col_pencils<float>(g.N, FftCfg<float>::kElems) : FftCfg<float>::kElems / g.N;
   if (g.S1 < 1 || g.x1_0 < 0 || g.x1_0 + g.S1 > g.N) return hipErrorInvalidValue;
   const int cb = (g.B2 + P - 1) / P;
   const int reps = loop_reps(g.S1, cb * nz);
   dim3 grid(cb, g.S1 / reps, nz);
   switch (g.N) {
-#define CASE(n) case n: hipLaunchKernelGGL((r2c_q2<n>), grid, dim3(kFftThreads), 0, st, H2, H1, tw, g, reps); break;
+#define CASE(n) case n: hipLaunchKernelGGL((r2c_q2<n, GRAD>), grid, dim3(kFftThreads), 0, st, H2, H1, tw, g, reps); break;
     PS_FOR_EACH_N(CASE)
 #undef CASE
     default: return hipErrorInvalidValue;
@@ -654,7 +657,7 @@ hipError_t launch_r2c_q2(const cplx<float>* H2, cplx<float>* H1, const cplx<floa
 template <bool MASK>
 hipError_t launch_r2c_q1(const cplx<float>* H1, const int16_t* sq, const int* qmax, cplx<float>* box,
                          const cplx<float>* tw, Geom g, int nz, hipStream_t st) {
-  const int P = col_pencils<float>(g.N, FftCfg<float>::kElems);
+  const int P = MASK ? col_pencils<float>(g.N, FftCfg<float>::kElems) : FftCfg<float>::kElems / g.N;
   dim3 grid((g.B0 + P - 1) / P, g.B2, nz);
   switch (g.N) {
 #define CASE(n) \
@@ -695,6 +698,8 @@ template hipError_t launch_c2r_p2<float>(const cplx<float>*, const int*, cplx<fl
                                          int, hipStream_t);
 template hipError_t launch_c2r_p2<double>(const cplx<double>*, const int*, cplx<double>*, const cplx<double>*,
                                           Geom, int, hipStream_t);
+template hipError_t launch_r2c_q2<true>(const cplx<float>*, cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
+template hipError_t launch_r2c_q2<false>(const cplx<float>*, cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
 template hipError_t launch_r2c_q1<true>(const cplx<float>*, const int16_t*, const int*, cplx<float>*,
                                         const cplx<float>*, Geom, int, hipStream_t);
 template hipError_t launch_r2c_q1<false>(const cplx<float>*, const int16_t*, const int*, cplx<float>*,

@@ -29,8 +29,10 @@ __device__ __forceinline__ void dft4(cplx<T>& x0, cplx<T>& x1, cplx<T>& x2, cplx
   x3 = csub(b, d);
 }
 
-template <typename T, int S>
-__device__ __forceinline__ void dft8(cplx<T>* v) {
+// PINNED (S > 0): which product of o1 is the rounded one, its real part's if `late`, else its
+// imaginary part's, is written out.
+template <typename T, int S, bool PINNED = false>
+__device__ __forceinline__ void dft8(cplx<T>* v, bool late = false) {
   cplx<T> e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
   cplx<T> o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
   dft4<T, S>(e0, e1, e2, e3);
@@ -40,6 +42,11 @@ __device__ __forceinline__ void dft8(cplx<T>* v) {
   cplx<T> t1 = cmul(o1, cplx<T>{h, (T)S * h});
   cplx<T> t2 = cmul_i(o2, S);
   cplx<T> t3 = cmul(o3, cplx<T>{-h, (T)S * h});
+  if constexpr (PINNED) {
+    static_assert(S > 0, "the inverse transform");
+    const T x = late ? o1.im : o1.re, y = (late ? o1.re : o1.im) * h;
+    t1 = {__builtin_fmaf(x, late ? -h : h, late ? y : -y), __builtin_fmaf(x, h, y)};
+  }
   v[0] = cadd(e0, o0);
   v[4] = csub(e0, o0);
   v[1] = cadd(e1, t1);
@@ -107,8 +114,13 @@ __device__ __forceinline__ void build_stage_twiddles(cplx<T>* stw, const cplx<T>
 // One Stockham stage of radix R over P pencils of length N stored with stride NS.
 // After the stage every run of p*R consecutive outputs is a finished sub-DFT.
 // tws: this stage's twiddle table, entry (r - 1) * p + k = exp(2 pi i k r / (p R)).
-template <typename T, int N, int P, int NS, int R, int S, int NT = kFftThreads>
-__device__ __forceinline__ void fft_stage(cplx<T>* buf, int p, const cplx<T>* tws) {
+//
+// PO, pen0: the pencils are pen0 .. pen0 + P - 1 of PO, and the values are bit for bit those of
+// a block that holds all PO.  There the compiler rounds, of the two products in one element times
+// an eighth root, one in the last NT butterflies of the second stage and the other in the rest;
+// where P differs from PO that choice is written out.  (Inverse transforms only.)
+template <typename T, int N, int P, int NS, int R, int S, int NT = kFftThreads, int PO = P>
+__device__ __forceinline__ void fft_stage(cplx<T>* buf, int p, const cplx<T>* tws, int pen0 = 0) {
   constexpr int NB = N / R;
   constexpr int BPT = (P * NB) / NT;
   static_assert(BPT >= 1 && (P * NB) % NT == 0, "block shape");
@@ -130,7 +142,12 @@ __device__ __forceinline__ void fft_stage(cplx<T>* buf, int p, const cplx<T>* tw
       }
       v[u][r] = x;
     }
-    dftR<T, S, R>(v[u]);
+    if constexpr (PO != P && S > 0 && R == 8) {
+      if (p > 1) dft8<T, S, true>(v[u], pen0 + pen >= PO - NT / NB);
+      else dft8<T, S>(v[u]);
+    } else {
+      dftR<T, S, R>(v[u]);
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -147,20 +164,20 @@ __device__ __forceinline__ void fft_stage(cplx<T>* buf, int p, const cplx<T>* tw
 }
 
 // Full length-N transform of the P pencils in buf (caller has synchronised).
-template <typename T, int N, int P, int NS, int S, int NT = kFftThreads>
-__device__ __forceinline__ void fft_block(cplx<T>* buf, const cplx<T>* stw) {
+template <typename T, int N, int P, int NS, int S, int NT = kFftThreads, int PO = P>
+__device__ __forceinline__ void fft_block(cplx<T>* buf, const cplx<T>* stw, int pen0 = 0) {
   int p = 1, off = 0;
   constexpr int L2 = __builtin_ctz(N);
   constexpr int N8 = L2 / 3;
   constexpr int REM = L2 % 3;
 #pragma unroll
   for (int st = 0; st < N8; ++st) {
-    fft_stage<T, N, P, NS, 8, S, NT>(buf, p, stw + off);
+    fft_stage<T, N, P, NS, 8, S, NT, PO>(buf, p, stw + off, pen0);
     if (p > 1) off += 7 * p;
     p *= 8;
   }
-  if constexpr (REM == 2) fft_stage<T, N, P, NS, 4, S, NT>(buf, p, stw + off);
-  if constexpr (REM == 1) fft_stage<T, N, P, NS, 2, S, NT>(buf, p, stw + off);
+  if constexpr (REM == 2) fft_stage<T, N, P, NS, 4, S, NT, PO>(buf, p, stw + off, pen0);
+  if constexpr (REM == 1) fft_stage<T, N, P, NS, 2, S, NT, PO>(buf, p, stw + off, pen0);
 }
 
 }  // namespace ps

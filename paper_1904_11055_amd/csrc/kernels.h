@@ -20,6 +20,7 @@ hipError_t launch_c2r_p3(const cplx<float>* H2, const int* qmax, float* out, uns
 hipError_t launch_c2r_p3_wedge(const cplx<double>* H2, const int* qmax, const int* rows, int nrows, double* out,
                                long long nwedge, const cplx<double>* tw, Geom g, int nz, hipStream_t st);
 hipError_t launch_r2c_q3(const float* in, cplx<float>* H2, const cplx<float>* tw, Geom g, int nz, hipStream_t st);
+template <bool GRAD>
 hipError_t launch_r2c_q2(const cplx<float>* H2, cplx<float>* H1, const cplx<float>* tw, Geom g, int nz,
                          hipStream_t st);
 template <bool MASK>

@@ -1299,7 +1299,7 @@ static polyspec_status shells_impl(polyspec_plan_t p, const void* d_delta) {
   } else {
     // the input transform uses H2 and H1 as scratch (sized for it in streamed plans too)
     PS_TIMED(p, POLYSPEC_PH_INPUT_Q3, ps::launch_r2c_q3((const float*)d_delta, p->H2, (const cplx<float>*)p->tw32.p, gin, p->batch, st));
-    PS_TIMED(p, POLYSPEC_PH_INPUT_Q2, ps::launch_r2c_q2(p->H2, p->H1, (const cplx<float>*)p->tw32.p, gin, p->batch, st));
+    PS_TIMED(p, POLYSPEC_PH_INPUT_Q2, ps::launch_r2c_q2<false>(p->H2, p->H1, (const cplx<float>*)p->tw32.p, gin, p->batch, st));
     PS_TIMED(p, POLYSPEC_PH_INPUT_Q1, ps::launch_r2c_q1<false>(p->H1, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, p->box,
                                        (const cplx<float>*)p->tw32.p, gin, p->batch, st));
   }
@@ -1552,7 +1552,7 @@ polyspec_status polyspec_backward(polyspec_plan_t p, const double* d_grad_out, v
                                         (const int*)p->pmask_d.p, p->absmax, p->rowmax, p->nb, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
                                         gk, p->batch, st));
     if (!fused) PS_TIMED(p, POLYSPEC_PH_ADJ_Q3, ps::launch_r2c_q3(p->A, p->H2, tw, gk, nz, st));
-    PS_TIMED(p, POLYSPEC_PH_ADJ_Q2, ps::launch_r2c_q2(p->H2, H1x, tw, gk, nz, st));
+    PS_TIMED(p, POLYSPEC_PH_ADJ_Q2, ps::launch_r2c_q2<true>(p->H2, H1x, tw, gk, nz, st));
     return POLYSPEC_OK;
   };
   if (p->streamed) {
