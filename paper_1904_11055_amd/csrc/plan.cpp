@@ -110,7 +110,6 @@ struct polyspec_plan_s {
   std::vector<int> wmask_host;     // adjoint: per v, bits 2 uc + mb of weight blocks
   std::vector<int> pmask_host;     // order-4 adjoint: per l, the pairs of partners with a weight
   bool jsched = false, j_all_used = false;
-  int j_load = 0;   // four times the largest number of its tiles on one SIMD
   int n_tiles_j = 0, ksteps_j = 0, n_chunks_j = 0;
 
   // device tables
@@ -751,9 +750,6 @@ polyspec_status build_jsched(polyspec_plan_s* p, std::vector<int>* ent_of_cand) 
       mask[w] |= 1u << s;
     }
   p->n_tiles_j = id;
-  int per_simd[4] = {};
-  for (int w = 0; w < ps::kJWaves; ++w) per_simd[w % 4] += __builtin_popcount(mask[w]);
-  p->j_load = 4 * *std::max_element(per_simd, per_simd + 4);
   // slots of each kind (the corners of contract_j3 left out), as far as the plan's blocks go
   p->j_all_used = true;
   for (int w = 0; w < ps::kJWaves; ++w) {
@@ -1326,16 +1322,13 @@ polyspec_status polyspec_shells(polyspec_plan_t p, const void* d_delta) {
 }
 
 // Whether an order-3 plan contracts by contract_j3 (products aligned to shell blocks) or by the
-// pair tiles of contract_tiles.  FP16: always.  FP32 spends its time in the matrix products
-// alone, so it takes the schedule with fewer tiles on its busiest SIMD (256^3: 40 shells, 96
-// against 84 pair tiles, 6.34 against 5.91 ms; 48 shells, 96 against 106, 6.64 against 7.76);
-// BF16 forms fewer operands the aligned way, which pays for 15% more tiles (40 shells 2.96
-// against 3.26 ms; 33 shells, 80 against 68 tiles, 2.70 against 2.39).  Plans of one shell
-// block are bound by the staging and take it always (13 shells: FP32 0.75 against 0.89 ms).
+// pair tiles of contract_tiles.  FP16: always.  FP32 and BF16: plans of one shell block, which are
+// bound by the staging (256^3, 13 shells, FP32: 0.75 against 0.89 ms), where the chunks are
+// whole 256-point stages; the sums are then the same bit for bit.  (Above 32 shells the aligned
+// products multiply j and k first, so the sums of some tuples would differ in the ninth digit.)
 static bool uses_j3(const polyspec_plan_s* p) {
   if (!p->jsched) return false;
-  if (p->prec == POLYSPEC_SPLIT_FP16 || p->n_blk == 1) return true;
-  return p->j_load <= p->n_tiles * (p->prec == POLYSPEC_SPLIT_BF16 ? 1.15 : 1.0);
+  return p->prec == POLYSPEC_SPLIT_FP16 || (p->n_blk == 1 && p->ksteps_j == p->ksteps);
 }
 
 // One contraction launch over the fields in D (the whole grid or one slab) and its

@@ -58,6 +58,5 @@ def test_aliased(gpu, nb):
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("nb", [9, 16, 40, 48, 49, 63, 64])
 def test_other_precisions(gpu, nb, precision):
-    """FP32 and BF16 on the plans that take the aligned products (one block; 48 and more), and
-    on one that chooses by precision (40)."""
+    """FP32 and BF16 on the plans that take the aligned products (one block), and on others."""
     _check(64, nb, 0.25, False, 64, precision)
