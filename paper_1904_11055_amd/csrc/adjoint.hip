@@ -5,14 +5,14 @@
 
 namespace ps {
 
-extern template hipError_t launch_adjoint_sym_prec<kFP32>(const float*, const uint4*, int, int, long long, float*,
+extern template hipError_t launch_adjoint_sym_prec<kFP32>(const float*, const uint4*, const float2*, int, int, long long, float*,
                                                           cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
-extern template hipError_t launch_adjoint_sym_prec<kBF16>(const float*, const uint4*, int, int, long long, float*,
+extern template hipError_t launch_adjoint_sym_prec<kBF16>(const float*, const uint4*, const float2*, int, int, long long, float*,
                                                           cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
-extern template hipError_t launch_adjoint4_sym_prec<kFP32>(const float*, const uint4*, const int*, int, long long,
+extern template hipError_t launch_adjoint4_sym_prec<kFP32>(const float*, const uint4*, const float2*, const int*, int, long long,
                                                            float*, cplx<float>*, const cplx<float>*, Geom, int,
                                                            hipStream_t);
-extern template hipError_t launch_adjoint4_sym_prec<kBF16>(const float*, const uint4*, const int*, int, long long,
+extern template hipError_t launch_adjoint4_sym_prec<kBF16>(const float*, const uint4*, const float2*, const int*, int, long long,
                                                            float*, cplx<float>*, const cplx<float>*, Geom, int,
                                                            hipStream_t);
 hipError_t launch_adjoint4_gemm_fp16(const float*, const uint4*, const int*, const unsigned*, const unsigned long long*,
@@ -133,6 +133,14 @@ __global__ void adjoint_weights(const double* __restrict__ grad, const double* _
   adj_store_weight(base, ln, r, w, kFP16);
 }
 
+// A weight of sym_equal: the value that the split's words hold, and the lo word.
+__device__ __forceinline__ float2 equal_weight(double w, int prec) {
+  const float x = (float)w;
+  if (prec != kBF16) return make_float2(x, 0.f);
+  const float h = __uint_as_float(__float_as_uint(x) & 0xffff0000u), l = (float)(__bf16)(x - h);
+  return make_float2(h + l, l);
+}
+
 // Lane ln of weight block idx (sym_index) of a pair of partners in shell block kb: which of
 // the two partners (t), the row m and the 16-shell chunk uc of u it holds.  Lane l is
 // chain row l % 32 and u = 16 uc + 8 (l / 32) + r; row rho is 16-row half rho / 16 and
@@ -156,11 +164,12 @@ __device__ __forceinline__ void sym_lane(int kb, int idx, int ln, int& t, int& m
 }
 
 // Order 3, symmetric form (FP32 and BF16): the matrices dQ_k/dd_m, W[b][pair][block][hi, lo]
-// [lane] with the blocks of sym_index, zero outside m, u <= k.
+// [lane] with the blocks of sym_index, zero outside m, u <= k.  The tuple of three times k is
+// left out (sym_equal adds it): its weight 3 w goes to equal[b][k].
 // grid (pairs of whole shell blocks, 16, batch), threads lane.
 __global__ void adjoint_sym_weights(const double* __restrict__ grad, const double* __restrict__ fnorm,
                                     const int* __restrict__ lookup, int n_shells, int n_closing, int prec,
-                                    uint4* __restrict__ W) {
+                                    uint4* __restrict__ W, float2* __restrict__ equal) {
   const int ln = threadIdx.x, pair = blockIdx.x, idx = blockIdx.y, b = blockIdx.z;
   const int kb = pair / 8;
   if (idx >= sym_blocks(kb)) return;
@@ -177,6 +186,10 @@ __global__ void adjoint_sym_weights(const double* __restrict__ grad, const doubl
       const size_t lo = m < u ? m : u, hi = m < u ? u : m;
       const int id = lookup[(lo * n_shells + hi) * n_shells + k];
       if (id >= 0) w = (m == u ? 2.0 : 1.0) * grad[(size_t)b * n_closing + id] * fnorm[id];
+      if (m == k && u == k) {
+        equal[b * 64 + k] = equal_weight(id >= 0 ? 3.0 * grad[(size_t)b * n_closing + id] * fnorm[id] : 0.0, prec);
+        w = 0.0;
+      }
     }
     adj_store_weight(base, ln, r, w, prec);
   }
@@ -188,7 +201,7 @@ __global__ void adjoint_sym_weights(const double* __restrict__ grad, const doubl
 // grid (blocks of the last l, n_shells: l, batch), threads lane.
 __global__ void adjoint4_sym_weights(const double* __restrict__ grad, const double* __restrict__ fnorm,
                                      const int* __restrict__ lookup, int n_shells, int n_closing, int prec,
-                                     uint4* __restrict__ W) {
+                                     uint4* __restrict__ W, float2* __restrict__ equal) {
   const int ln = threadIdx.x, l = blockIdx.y, b = blockIdx.z;
   if ((int)blockIdx.x >= sym4_blocks_of(l)) return;
   int kb = 0;
@@ -208,6 +221,10 @@ __global__ void adjoint4_sym_weights(const double* __restrict__ grad, const doub
       const int id = lookup[(((size_t)t[0] * n_shells + t[1]) * n_shells + t[2]) * n_shells + l];
       const int mult = kb == 0 ? (m == t[0]) + (m == t[1]) + (m == t[2]) : m == u ? 2 : 1;
       if (id >= 0) w = (double)mult * grad[(size_t)b * n_closing + id] * fnorm[id];
+      if (m == l && u == l && k == l) {
+        equal[b * 64 + l] = equal_weight(id >= 0 ? 4.0 * grad[(size_t)b * n_closing + id] * fnorm[id] : 0.0, prec);
+        w = 0.0;
+      }
     }
     adj_store_weight(base, ln, r, w, prec);
   }
@@ -258,7 +275,7 @@ hipError_t launch_adjoint_weights(const double* grad, const double* fnorm, const
                        n_closing, absmax, rowmax, W);
   else
     hipLaunchKernelGGL(adjoint_sym_weights, dim3((n_shells + 15) / 16 * 8, 16, batch), dim3(64), 0, st, grad, fnorm,
-                       lookup, n_shells, n_closing, prec, W);
+                       lookup, n_shells, n_closing, prec, W, reinterpret_cast<float2*>(rowmax));
   return hipGetLastError();
 }
 
@@ -279,7 +296,7 @@ hipError_t launch_adjoint4_weights(const double* grad, const double* fnorm, cons
                        n_closing, absmax, rowmax, W);
   else
     hipLaunchKernelGGL(adjoint4_sym_weights, dim3(sym4_blocks_of(n_shells - 1), n_shells, batch), dim3(64), 0, st, grad,
-                       fnorm, lookup, n_shells, n_closing, prec, W);
+                       fnorm, lookup, n_shells, n_closing, prec, W, reinterpret_cast<float2*>(rowmax));
   return hipGetLastError();
 }
 
@@ -289,8 +306,9 @@ hipError_t launch_adjoint_gemm(int prec, const float* D, const uint4* W, const i
   const bool fused = adjoint_fuses_rows(g.N);
   if (fused == (H2 == nullptr) || fused == (A != nullptr) || n_shells > 64 || G % kAdjPts != 0)
     return hipErrorInvalidValue;
-  if (prec == kFP32) return launch_adjoint_sym_prec<kFP32>(D, W, n_shells, dense, G, A, H2, tw, g, batch, st);
-  if (prec == kBF16) return launch_adjoint_sym_prec<kBF16>(D, W, n_shells, dense, G, A, H2, tw, g, batch, st);
+  const float2* equal = reinterpret_cast<const float2*>(rowmax);   // FP16 alone scales its rows
+  if (prec == kFP32) return launch_adjoint_sym_prec<kFP32>(D, W, equal, n_shells, dense, G, A, H2, tw, g, batch, st);
+  if (prec == kBF16) return launch_adjoint_sym_prec<kBF16>(D, W, equal, n_shells, dense, G, A, H2, tw, g, batch, st);
   return launch_adjoint_gemm_fp16(D, W, vmask, absmax, rowmax, n_shells, G, A, H2, tw, g, batch, st);
 }
 
@@ -300,8 +318,9 @@ hipError_t launch_adjoint4_gemm(int prec, const float* D, const uint4* W, const 
   const bool fused = adjoint_fuses_rows(g.N);
   if (fused == (H2 == nullptr) || fused == (A != nullptr) || n_shells > kAdj4MaxShells || G % kAdjPts != 0)
     return hipErrorInvalidValue;
-  if (prec == kFP32) return launch_adjoint4_sym_prec<kFP32>(D, W, pmask, n_shells, G, A, H2, tw, g, batch, st);
-  if (prec == kBF16) return launch_adjoint4_sym_prec<kBF16>(D, W, pmask, n_shells, G, A, H2, tw, g, batch, st);
+  const float2* equal = reinterpret_cast<const float2*>(rowmax);   // FP16 alone scales its rows
+  if (prec == kFP32) return launch_adjoint4_sym_prec<kFP32>(D, W, equal, pmask, n_shells, G, A, H2, tw, g, batch, st);
+  if (prec == kBF16) return launch_adjoint4_sym_prec<kBF16>(D, W, equal, pmask, n_shells, G, A, H2, tw, g, batch, st);
   return launch_adjoint4_gemm_fp16(D, W, imask, absmax, rowmax, n_shells, G, A, H2, tw, g, batch, st);
 }
 

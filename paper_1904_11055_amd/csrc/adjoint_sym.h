@@ -42,6 +42,32 @@ constexpr size_t sym_lds_bytes() {
   return adj_fft_lds_bytes<NF, KB>() > stage ? adj_fft_lds_bytes<NF, KB>() : stage;
 }
 
+// The tuples of one shell ORDER times, a_k += (weight) d_k^(ORDER - 1): most of the gradient of a
+// clustered field is theirs.  In the matrix products, k being the largest shell, their weight
+// would be 2 w (order 4: 3 w), whose BF16 words are others than those of the whole 3 w (4 w),
+// and the rounding of that one weight would set the gradient's error: 20 shells of width 2 at
+// 256^3, 0.5 to 3.4 times that of a product with one row per m over 12 inputs, 0.7 to 1.1 in
+// this form (128^3 x 8, order 3: 0.9 to 1.3, and 1.0).  equal[k]: the weight as its two
+// words hold it, and the lo word.
+// They start the accumulators, which costs no register.
+template <int PREC, int KB, int ORDER>
+__device__ __forceinline__ void sym_equal(float (&acc)[kAdjPB][KB][8], const AdjFields<PREC, KB>& f,
+                                          const Operand<PREC> (&fop)[kAdjPB][KB], const float2* equal, int hh) {
+#pragma unroll
+  for (int M = 0; M < KB; ++M)
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float2 w = equal[16 * M + 8 * hh + r];
+#pragma unroll
+      for (int pb = 0; pb < kAdjPB; ++pb) {
+        const float x = f.F[pb][M][r];
+        float y = w.x * x;
+        if constexpr (PREC == kBF16) y = fmaf(-w.y, (float)fop[pb][M].lo[r], y);   // what the matrix products drop
+        acc[pb][M][r] = (ORDER == 4 ? x * x : x) * y;
+      }
+    }
+}
+
 // COUNT blocks of a chain from chunk FROM (S: upwards; P: FROM-th below kb, downwards).
 template <int PREC, int KB, int kb, bool P, int M, int T, int FROM, int COUNT>
 __device__ __forceinline__ void sym_chain(f32x16 (&Y)[kAdjPB], const uint4* wv, const Operand<PREC> (&fop)[kAdjPB][KB],
@@ -106,7 +132,7 @@ __device__ __forceinline__ void sym_add(float (&acc)[kAdjPB][KB][8], float (&q)[
 // transform's paired stores: 75.4 with 8 waves).
 template <int PREC, int NF, int KB>
 __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __restrict__ D, const uint4* __restrict__ W,
-                                                            int n_shells, int dense, long long G,
+                                                            const float2* __restrict__ equal, int n_shells, int dense, long long G,
                                                             float* __restrict__ A, cplx<float>* __restrict__ H2,
                                                             const cplx<float>* __restrict__ tw, Geom g) {
   static_assert(PREC != kFP16, "the FP16 split scales every weight row by its own power of two: adjoint_gemm");
@@ -121,6 +147,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
   const float* Db = D + (size_t)b * n_shells * G;
   const uint4* Wb = W + (size_t)b * sym_base((n_shells + 15) / 16) * kSymBlockWords;
 
+  __shared__ float2 eqs[16 * KB];
+  if (tid < 16 * KB) eqs[tid] = tid < n_shells ? equal[b * 64 + tid] : make_float2(0.f, 0.f);
   AdjFields<PREC, KB> f;
   adj_load_fields<PREC, KB>(f, Db, G, xw, hh, n_shells, nullptr, b);
 #pragma unroll
@@ -132,14 +160,9 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
     for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
 
   float acc[kAdjPB][KB][8];
-#pragma unroll
-  for (int pb = 0; pb < kAdjPB; ++pb)
-#pragma unroll
-    for (int M = 0; M < KB; ++M)
-#pragma unroll
-      for (int r = 0; r < 8; ++r) acc[pb][M][r] = 0.f;
   const float half_of[2] = {hh == 0 ? 0.5f : 0.f, hh == 1 ? 0.5f : 0.f};
   __syncthreads();
+  sym_equal<PREC, KB, 3>(acc, f, fop, eqs, hh);
 
   // One stage: copy the next one in, then the pairs of this one.  The two buffers are
   // restrict parameters so that the compiler knows the reads of `now` not to touch the
@@ -241,6 +264,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
 // the products and a corner of k x k replaces 64 rows x every chunk.
 template <int PREC, int NF, int KB>
 __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __restrict__ D, const uint4* __restrict__ W,
+                                                             const float2* __restrict__ equal,
                                                              const int* __restrict__ pmask, int n_shells,
                                                              long long G, float* __restrict__ A,
                                                              cplx<float>* __restrict__ H2,
@@ -258,6 +282,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
   const int n_words = sym4_blocks(n_shells) * kSymBlockWords;
   const uint4* Wb = W + (size_t)b * n_words;
 
+  __shared__ float2 eqs[16 * KB];
+  if (tid < 16 * KB) eqs[tid] = tid < n_shells ? equal[b * 64 + tid] : make_float2(0.f, 0.f);
   AdjFields<PREC, KB> f;
   adj_load_fields<PREC, KB>(f, Db, G, xw, hh, n_shells, nullptr, b);
 #pragma unroll
@@ -271,18 +297,13 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
 #pragma unroll
     for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
   float acc[kAdjPB][KB][8];
-#pragma unroll
-  for (int pb = 0; pb < kAdjPB; ++pb)
-#pragma unroll
-    for (int M = 0; M < KB; ++M)
-#pragma unroll
-      for (int r = 0; r < 8; ++r) acc[pb][M][r] = 0.f;
   // d_l at the lane's points and the mask of l, one l ahead
   float dl_next[kAdjPB];
 #pragma unroll
   for (int pb = 0; pb < kAdjPB; ++pb) dl_next[pb] = Db[xw + 32 * pb];
   int pm_next = pmask[0];
   __syncthreads();
+  sym_equal<PREC, KB, 4>(acc, f, fop, eqs, hh);
 
   float dl[kAdjPB], al[kAdjPB];
   unsigned pm = 0;
@@ -429,10 +450,10 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
 }
 
 template <int PREC>
-hipError_t launch_adjoint_sym_prec(const float* D, const uint4* W, int n_shells, int dense, long long G, float* A,
+hipError_t launch_adjoint_sym_prec(const float* D, const uint4* W, const float2* equal, int n_shells, int dense, long long G, float* A,
                                    cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st) {
   dim3 grid((unsigned)(G / kAdjPts), batch);
-#define L2(NF, KB) hipLaunchKernelGGL((adjoint_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, n_shells, \
+#define L2(NF, KB) hipLaunchKernelGGL((adjoint_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, equal, n_shells, \
                                       dense, G, A, H2, tw, g)
 #define L(NF)                          \
   do {                                 \
@@ -455,11 +476,11 @@ hipError_t launch_adjoint_sym_prec(const float* D, const uint4* W, int n_shells,
 }
 
 template <int PREC>
-hipError_t launch_adjoint4_sym_prec(const float* D, const uint4* W, const int* pmask, int n_shells, long long G,
+hipError_t launch_adjoint4_sym_prec(const float* D, const uint4* W, const float2* equal, const int* pmask, int n_shells, long long G,
                                     float* A, cplx<float>* H2, const cplx<float>* tw, Geom g, int batch,
                                     hipStream_t st) {
   dim3 grid((unsigned)(G / kAdjPts), batch);
-#define L2(NF, KB) hipLaunchKernelGGL((adjoint4_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, pmask, \
+#define L2(NF, KB) hipLaunchKernelGGL((adjoint4_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, equal, pmask, \
                                       n_shells, G, A, H2, tw, g)
 #define L(NF)                           \
   do {                                  \

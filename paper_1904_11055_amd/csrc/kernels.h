@@ -140,7 +140,7 @@ hipError_t launch_counts_wedge(int order, const double* cw, long long nwedge, co
 hipError_t launch_reduce_dd(const double2* part, double2* tmp, int n_chunks, int cpg, int n_groups, long long n_ent,
                             hipStream_t st);
 // Adjoint products (adjoint.h).  FP16 (prec 2) scales every weight row m by its own
-// power of two, found from rowmax[b][64] (float64 bits, written by the weights launch);
+// power of two, found from rowmax[b][64] (float64 bits, written by the weights launch; FP32 and BF16 keep the weights of sym_equal there);
 // absmax holds the per-shell field maxima of the forward's FP16 scaling.
 hipError_t launch_adjoint_weights(const double* grad, const double* fnorm, const int* lookup, int n_shells,
                                   int n_closing, int prec, const unsigned* absmax, unsigned long long* rowmax,
