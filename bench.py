@@ -50,7 +50,7 @@ def kernel_source_hash() -> str:
     """Hash of the sources of the matrix-core kernels (the contraction and the adjoint)."""
     h = hashlib.sha256()
     for f in ("contract_tiles.h", "contract_tiles_lo.hip", "contract_tiles_hi.hip", "contract_j3.hip",
-              "adjoint.h", "adjoint.hip", "adjoint_fp16.hip", "adjoint4_fp16.hip", "adjoint_sym.h", "adjoint_sym_fp32.hip",
+              "contract_pairs.hip", "adjoint.h", "adjoint.hip", "adjoint_fp16.hip", "adjoint4_fp16.hip", "adjoint_sym.h", "adjoint_sym_fp32.hip",
               "adjoint_sym_bf16.hip", "adjoint4_sym_fp32.hip", "adjoint4_sym_bf16.hip",
               "mfma_ops.h", "fft_core.h", "common.h", "kernels.h"):
         with open(os.path.join(ROOT, "paper_1904_11055_amd", "csrc", f), "rb") as fh:
@@ -259,8 +259,12 @@ def main():
     # algorithmic flops per launch: 2 per (closing triplet x point) + 1 per (pair x point)
     # for the contraction; 2 per (adjoint weight x point) + 1 per (pair x point) for the
     # adjoint product, whatever the tiles the kernels actually issue
-    # the FP16 split of an order-3 plan runs the shell-block aligned kernel
-    ctr_kernel = "contract_j3" if (args.precision == "fp16" and order == 3 and nb <= 64) else "contract_tiles"
+    # the contraction kernel by order, precision and shells (order 3 in FP32 and BF16 takes the
+    # aligned products where they have fewer tiles)
+    ctr_kernel = ("contract_rows" if order >= 5 else
+                  "contract_pairs" if order == 4 and args.precision == "fp16" and nb <= 64 else
+                  "contract_j3" if order == 3 and nb <= 64 and (args.precision == "fp16" or nb <= 16 or nb >= 45) else
+                  "contract_tiles")
     # algorithmic flops: 2 per (closing tuple x point), plus the row products formed once
     # per point: 1 per pair (orders 3 to 5) and 2 per triple (orders 5 and 6)
     row_flops = (n_pairs if order <= 5 else 0) + (2 * n_triples if order >= 5 else 0)

@@ -19,7 +19,8 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpolyspec.so")
-SOURCES = ["fft.hip", "contract_tiles_lo.hip", "contract_tiles_hi.hip", "contract_j3.hip", "reduce.hip",
+SOURCES = ["fft.hip", "contract_tiles_lo.hip", "contract_tiles_hi.hip", "contract_j3.hip",
+           "contract_pairs.hip", "reduce.hip",
            "adjoint.hip", "adjoint_sym_fp32.hip", "adjoint_sym_bf16.hip", "adjoint4_sym_fp32.hip",
            "adjoint4_sym_bf16.hip", "adjoint_fp16.hip", "adjoint4_fp16.hip", "util.hip", "plan.cpp"]
 ARCH = "gfx950"

@@ -40,7 +40,6 @@ struct CtrParams {
   const int* slot_uni;     // [n_groups][waves][kSlots / 4]: one byte per slot
   const int* slot_lane;    // [n_groups][waves][16 rows][kSlots]: pair shells per lane
   const int* slot_tile;
-  const int* slot_blk;     // [n_groups][waves][kSlotsMax]: A pair block | B pair block << 16
   const unsigned* absmax;
   float* partials;
   long long G;
@@ -50,15 +49,10 @@ struct CtrParams {
   int n_tiles;
   int ksteps;
   int n_chunks;
-  int n_pair_blocks;       // order 4, FP16: pair operands formed once per K-step in LDS (0: per slot)
   const int* a_rows;       // orders 5 and 6: the A rows, staged row offsets of their shells (10 bits each)
-  const int* grp_blk;      // or null: [n_groups][kMaxPairBlocksHost] the group's own pair blocks (global ids);
-                           // orders 5 and 6: [n_groups][kHiABlocks] its A blocks
-  const int* grp_nblk;     // [n_groups]: how many (then slot_blk holds indices into that list)
+  const int* grp_blk;      // orders 5 and 6: [n_groups][kHiABlocks] the group's A blocks
+  const int* grp_nblk;     // [n_groups]: how many
 };
-// Order 4, split FP16: pair blocks that fit the workgroup's LDS as shared operands
-// beside the staged shell operands (28 blocks of 16 pairs: up to 29 shells).
-constexpr int kMaxPairBlocksHost = 28;
 constexpr int kCtrWavesHost = 16;
 constexpr int kSlotsHost = 14;
 constexpr int kSlots4Host = 10;
@@ -77,6 +71,30 @@ constexpr int kMaxTileBlkHost = 8;   // the tile kernel, orders 2 to 4 (<= 128 s
 constexpr int kAdjPtsHost = 512;   // grid points per adjoint workgroup
 constexpr int kCntTuplesPerGroup = 1024;
 constexpr int kCntStageHost = 32;
+
+// Order 4 in split FP16, up to 64 shells (contract_pairs.hip): slots of `tiles` A blocks
+// (aligned to that number) against one B block, `slots` per wave; k4Blocks pair blocks are what
+// fits the workgroup's LDS beside the staged shell operands, one half of a stage.
+struct Ctr4Shape { int waves, slots, tiles, blocks; };
+constexpr int k4Blocks = 56;
+constexpr Ctr4Shape k4Narrow = {16, 8, 2, k4Blocks / 2};
+constexpr Ctr4Shape k4Wide = {8, 10, 4, k4Blocks};
+struct Ctr4Params {
+  const float* D;
+  const unsigned* absmax;
+  const int* pair_uv;
+  const int* slot_a;       // [n_groups][waves][slots]: the group's indices of the A blocks, a byte each
+  const int* slot_b;       // [n_groups][waves][slots]: bits 0-7 the B block; 8: load the A blocks; 9, 10:
+                           // the first, last two tiles in use; < 0: empty
+  const int* slot_tile;    // [n_groups][waves][slots][tiles]: tile ids, or -1
+  const int* grp_blk;      // [n_groups][k4Blocks]: the group's pair blocks
+  const int* grp_nblk;
+  float* partials;
+  long long G;
+  int n_shells, n_blk, n_tiles, ksteps, n_chunks;
+  bool wide;               // the shape of the tables
+};
+hipError_t launch_contract_pairs(const Ctr4Params& p, int n_groups, int batch, hipStream_t st);
 
 hipError_t launch_contract(int prec, int order, const CtrParams& p, int n_groups, int batch, hipStream_t st);
 

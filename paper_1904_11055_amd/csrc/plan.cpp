@@ -113,13 +113,14 @@ struct polyspec_plan_s {
   int n_tiles_j = 0, ksteps_j = 0, n_chunks_j = 0;
 
   // device tables
-  DevBuf tw32, shell_q, qmax_d, pairs_d, slots_d, slot_lane_d, slot_tile_d, slot_blk_d, ent_d, bins_d, fnorm_d, lookup_d,
+  DevBuf tw32, shell_q, qmax_d, pairs_d, slots_d, slot_lane_d, slot_tile_d, ent_d, bins_d, fnorm_d, lookup_d,
       wmask_d, pmask_d, flag_d;
   DevBuf jtile_d, jmask_d, ent_j_d;
-  // order 4 with more pair blocks than one workgroup's LDS holds: each tile group's own
-  // pair blocks (global ids, kMaxPairBlocksHost per group) and their count
-  bool pair_groups = false;
   DevBuf grp_blk_d, grp_nblk_d;   // orders 5 and 6: the A blocks of each tile group
+  // order 4 up to 64 shells: the schedule of contract_pairs (FP16)
+  int n_groups4 = 0;
+  bool wide4 = false;
+  DevBuf sa4_d, sb4_d, tile4_d, grp4_d, ngrp4_d;
   DevBuf a_rows_d;                // orders 5 and 6: staged row offsets of the A rows
   DevBuf closing_of_ent_d, closing_of_ent_j_d;   // streamed plans: tile entry -> closing tuple (or -1)
   // workspace carving
@@ -535,6 +536,101 @@ polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& 
   return POLYSPEC_OK;
 }
 
+// Order 4 in split FP16: slots of `tiles` aligned A blocks against one B block.  Groups hold up
+// to waves x slots of them and the pair blocks that the shape's LDS has room for, and form
+// only their own blocks; they are cut from a grid of ka A blocks by kb B blocks.  The grid is
+// the cheapest by cycles of a SIMD per half stage: about 1000 for staging and the barriers of
+// each group, 80 per block formed, 12 per tile of the longest wave's slots times the waves
+// (40 unit shells at N = 256: 26.1 ms; 27.0 with the fewest groups).  Slots go to the waves in
+// (A, B) order, runs of equal length, the longer by one on the first waves: waves w, w + 4, ...
+// share a SIMD, so no SIMD gets more than one slot more than another (30 shells: 10.9 -> 10.4).
+polyspec_status pack_order4(polyspec_plan_s* p, const std::vector<TileKey>& tlist) {
+  const int npb = p->n_pairs_padded / 16;
+  p->wide4 = npb > ps::k4Narrow.blocks;
+  const ps::Ctr4Shape shape = p->wide4 ? ps::k4Wide : ps::k4Narrow;
+  const int W = shape.waves, NS = shape.slots, T = shape.tiles, cap = W * NS, lmax = shape.blocks;
+  std::map<std::pair<int, int>, std::array<int, 4>> slots;   // (A / T, B) -> tile ids
+  for (size_t t = 0; t < tlist.size(); ++t) {
+    auto it = slots.insert({{tlist[t].a / T, tlist[t].b}, {-1, -1, -1, -1}}).first;
+    it->second[tlist[t].a % T] = (int)t;
+  }
+  using Slot = std::pair<std::pair<int, int>, std::array<int, 4>>;
+  // the groups of a grid of ka x kb rectangles
+  auto cut = [&](int ka, int kb) {
+    std::map<std::pair<int, int>, std::vector<Slot>> rect;
+    for (const auto& kv : slots) rect[{T * kv.first.first / ka, kv.first.second / kb}].push_back(kv);
+    std::vector<std::vector<Slot>> groups;
+    for (const auto& kv : rect) {
+      const size_t n = kv.second.size(), n_grp = (n + cap - 1) / cap, per = (n + n_grp - 1) / n_grp;
+      for (size_t f = 0; f < n; f += per)
+        groups.emplace_back(kv.second.begin() + f, kv.second.begin() + std::min(n, f + per));
+    }
+    return groups;
+  };
+  auto blocks_of = [&](const std::vector<Slot>& g) {
+    std::vector<int> blocks;
+    for (const Slot& s : g) {
+      for (int a = 0; a < T; ++a)
+        if (s.second[a] >= 0) blocks.push_back(T * s.first.first + a);
+      blocks.push_back(s.first.second);
+    }
+    std::sort(blocks.begin(), blocks.end());
+    blocks.erase(std::unique(blocks.begin(), blocks.end()), blocks.end());
+    return blocks;
+  };
+  std::vector<std::vector<Slot>> groups;
+  double best = -1;
+  const int step = npb > 64 ? 8 : 4;
+  for (int ka = step; ka < npb + step; ka += step)
+    for (int kb = step; kb < npb + step; kb += step) {
+      if (std::min(ka, npb) + std::min(kb, npb) > lmax && npb > lmax) continue;
+      std::vector<std::vector<Slot>> g = cut(ka, kb);
+      double cost = 0;   // see above
+      for (const auto& x : g)
+        cost += 1000.0 + 80.0 * (double)blocks_of(x).size() + 48.0 * T / 4.0 * (double)(((int)x.size() + W - 1) / W * W);
+      if (best < 0 || cost < best) { best = cost; groups = std::move(g); }
+    }
+  std::vector<int> sa, sb, tile, grp, ngrp;
+  for (const auto& all : groups) {
+    const int cnt = (int)all.size();
+    std::vector<int> blocks = blocks_of(all);
+    if ((int)blocks.size() > lmax) return p->fail(POLYSPEC_ERR_UNSUPPORTED, "tile group exceeds its pair blocks");
+    // a block that the group does not form is the A block of no tile: any index will do
+    auto local = [&](int id) {
+      auto it = std::lower_bound(blocks.begin(), blocks.end(), id);
+      return it != blocks.end() && *it == id ? (int)(it - blocks.begin()) : 0;
+    };
+    const size_t b0 = sb.size();
+    sa.resize(b0 + (size_t)W * NS, 0);
+    sb.resize(b0 + (size_t)W * NS, -1);
+    tile.resize((b0 + (size_t)W * NS) * T, -1);
+    for (int w = 0, k0 = 0, n = 0; w < W; ++w, k0 += n) {
+      n = cnt / W + (w < cnt % W);
+      for (int k = 0; k < n; ++k) {
+        const Slot& sl = all[k0 + k];
+        const size_t at = b0 + (size_t)w * NS + k;
+        const bool load = k == 0 || all[k0 + k - 1].first.first != sl.first.first;
+        for (int a = 0; a < T; ++a) {
+          sa[at] |= local(T * sl.first.first + a) << (8 * a);
+          tile[at * T + a] = sl.second[a];
+        }
+        sb[at] = local(sl.first.second) | (load ? 0x100 : 0) | (sl.second[0] >= 0 || sl.second[1] >= 0 ? 0x200 : 0) |
+                 (sl.second[2] >= 0 || sl.second[3] >= 0 ? 0x400 : 0);
+      }
+    }
+    ngrp.push_back((int)blocks.size());
+    blocks.resize(ps::k4Blocks, 0);
+    grp.insert(grp.end(), blocks.begin(), blocks.end());
+    ++p->n_groups4;
+  }
+  PS_TRY(upload(p, &p->sa4_d, sa));
+  PS_TRY(upload(p, &p->sb4_d, sb));
+  PS_TRY(upload(p, &p->tile4_d, tile));
+  PS_TRY(upload(p, &p->grp4_d, grp));
+  PS_TRY(upload(p, &p->ngrp4_d, ngrp));
+  return POLYSPEC_OK;
+}
+
 polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   std::vector<int> pidx;
   build_pairs(p, &pidx);
@@ -604,71 +700,26 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   };
   std::vector<std::vector<Wave>> groups;
   auto new_group = [&]() { groups.emplace_back(ps::kCtrWavesHost); };
-  // Order 4 in split FP16 with more pair blocks than fit one workgroup's LDS as shared
-  // operands: tile groups over rectangles of ka A blocks by kb B blocks (ka + kb within the
-  // LDS), the rectangle sizes that give the fewest groups; each group then forms only its
-  // own blocks, once per K-step.  Tiles go to the waves in (A, B) order, a contiguous run
-  // each.  The grouping follows the precision the plan is made with: the FP32 and BF16
-  // contractions, which form pair products per tile, run faster on the greedy groups
-  // below (40 shells at 256^3, FP32: 77 against 83 ms); after a switch of precision the
-  // plan keeps its grouping (a plan made in FP32 then contracts FP16 without the sharing).
-  const int npb = p->n_pairs_padded / 16;
-  const int lmax = ps::kMaxPairBlocksHost;
-  p->pair_groups = n == 4 && p->prec == POLYSPEC_SPLIT_FP16 && p->n_blk <= 4 && npb > lmax;
-  std::vector<int> grp_blk, grp_nblk;
-  if (p->pair_groups) {
-    int best = -1, bka = 0, bkb = 0;
-    for (int ka = 1; ka < lmax; ++ka)
-      for (int kb = 1; ka + kb <= lmax; ++kb) {
-        std::map<std::pair<int, int>, int> cnt;
-        for (const TileKey& k : tlist) ++cnt[{k.a / ka, k.b / kb}];
-        int ng = 0;
-        for (const auto& kv : cnt) ng += (kv.second + 16 * cap - 1) / (16 * cap);
-        if (best < 0 || ng < best) { best = ng; bka = ka; bkb = kb; }
-      }
-    std::map<std::pair<int, int>, std::vector<int>> rect;   // tiles in (A, B) order
-    for (int t = 0; t < id; ++t) rect[{tlist[t].a / bka, tlist[t].b / bkb}].push_back(t);
-    for (const auto& kv : rect) {
-      const std::vector<int>& tl = kv.second;
-      for (size_t f = 0; f < tl.size(); f += 16 * cap) {
-        const int cnt = (int)std::min(tl.size() - f, (size_t)16 * cap);
-        new_group();
-        const int per = (cnt + ps::kCtrWavesHost - 1) / ps::kCtrWavesHost;
-        for (int k = 0; k < cnt; ++k) groups.back()[k / per].tiles.push_back(tl[f + k]);
-        std::vector<int> blocks;
-        for (int k = 0; k < cnt; ++k) {
-          blocks.push_back(tlist[tl[f + k]].a);
-          blocks.push_back(tlist[tl[f + k]].b);
-        }
-        std::sort(blocks.begin(), blocks.end());
-        blocks.erase(std::unique(blocks.begin(), blocks.end()), blocks.end());
-        if ((int)blocks.size() > lmax) return p->fail(POLYSPEC_ERR_UNSUPPORTED, "tile group exceeds its pair blocks");
-        grp_nblk.push_back((int)blocks.size());
-        blocks.resize(lmax, -1);
-        grp_blk.insert(grp_blk.end(), blocks.begin(), blocks.end());
-      }
+  if (n == 4 && p->n_blk <= ps::kMaxBlkHost) PS_TRY(pack_order4(p, tlist));
+  // greedy: largest units first, onto the least loaded wave with room
+  std::vector<int> order(units.size());
+  for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int x, int y) { return units[x].second > units[y].second; });
+  new_group();
+  for (int ui : order) {
+    const int cnt = units[ui].second;
+    if (cnt > cap) return p->fail(POLYSPEC_ERR_UNSUPPORTED, "tile unit larger than a wave");
+    Wave* best = nullptr;
+    for (auto& grp : groups)
+      for (auto& w : grp)
+        if ((int)w.tiles.size() + cnt <= cap && (!best || w.load < best->load)) best = &w;
+    if (!best) {
+      new_group();
+      best = &groups.back()[0];
     }
-  } else {
-    // greedy: largest units first, onto the least loaded wave with room
-    std::vector<int> order(units.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int x, int y) { return units[x].second > units[y].second; });
-    new_group();
-    for (int ui : order) {
-      const int cnt = units[ui].second;
-      if (cnt > cap) return p->fail(POLYSPEC_ERR_UNSUPPORTED, "tile unit larger than a wave");
-      Wave* best = nullptr;
-      for (auto& grp : groups)
-        for (auto& w : grp)
-          if ((int)w.tiles.size() + cnt <= cap && (!best || w.load < best->load)) best = &w;
-      if (!best) {
-        new_group();
-        best = &groups.back()[0];
-      }
-      for (int k = 0; k < cnt; ++k) best->tiles.push_back(units[ui].first + k);
-      best->load += 1.0 + cnt * (n == 4 ? 2.0 : 1.0);   // one A formation + the tiles
-    }
+    for (int k = 0; k < cnt; ++k) best->tiles.push_back(units[ui].first + k);
+    best->load += 1.0 + cnt * (n == 4 ? 2.0 : 1.0);   // one A formation + the tiles
   }
   p->n_groups = (int)groups.size();
   // slot tables (see contract_tiles): a uniform byte per slot and per-lane pair shells,
@@ -677,7 +728,6 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   std::vector<int> uni((size_t)p->n_groups * ps::kCtrWavesHost * (S / 4), 0);
   std::vector<int> lanew((size_t)p->n_groups * ps::kCtrWavesHost * 16 * S, 0);
   std::vector<int> slot_tile((size_t)p->n_groups * ps::kCtrWavesHost * S, -1);
-  std::vector<int> slot_blk((size_t)p->n_groups * ps::kCtrWavesHost * S, 0);   // A | B << 16 pair blocks
   auto uv8 = [&](int pair) {
     const int w = p->pair_uv[pair];
     return (w & 0xff) | (((w >> 16) & 0xff) << 8);
@@ -700,13 +750,6 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
           prev_a = k.a;
           info = (n == 4 ? 0 : (k.b & 7)) | (n == 2 ? (k.a & 7) << 3 : 0) | (form << 6);
           slot_tile[gw * S + s] = tl[s];
-          if (p->pair_groups) {   // the group's local block indices
-            const int* gb = &grp_blk[(size_t)gi * lmax];
-            const int la = (int)(std::find(gb, gb + lmax, k.a) - gb), lb = (int)(std::find(gb, gb + lmax, k.b) - gb);
-            slot_blk[gw * S + s] = la | (lb << 16);
-          } else {
-            slot_blk[gw * S + s] = k.a | (k.b << 16);
-          }
           for (int r = 0; r < 16; ++r) {
             int* row_words = &lanew[(gw * 16 + r) * S];
             if (n == 3) row_words[s / 2] |= uv8(16 * k.a + r) << (16 * (s % 2));
@@ -719,12 +762,7 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   PS_TRY(upload(p, &p->slots_d, uni));
   PS_TRY(upload(p, &p->slot_lane_d, lanew));
   PS_TRY(upload(p, &p->slot_tile_d, slot_tile));
-  PS_TRY(upload(p, &p->slot_blk_d, slot_blk));
   PS_TRY(upload(p, &p->pairs_d, p->pair_uv));
-  if (p->pair_groups) {
-    PS_TRY(upload(p, &p->grp_blk_d, grp_blk));
-    PS_TRY(upload(p, &p->grp_nblk_d, grp_nblk));
-  }
   return POLYSPEC_OK;
 }
 
@@ -1137,9 +1175,9 @@ void release(polyspec_plan_s* p) {
   p->ev_pending.clear();
   for (hipEvent_t e : p->ev_pool) (void)hipEventDestroy(e);
   p->ev_pool.clear();
-  DevBuf* bufs[] = {&p->tw32, &p->shell_q, &p->qmax_d, &p->pairs_d, &p->slots_d, &p->slot_lane_d, &p->slot_tile_d, &p->slot_blk_d, &p->ent_d,
+  DevBuf* bufs[] = {&p->tw32, &p->shell_q, &p->qmax_d, &p->pairs_d, &p->slots_d, &p->slot_lane_d, &p->slot_tile_d,   &p->ent_d,
                     &p->bins_d, &p->fnorm_d, &p->lookup_d, &p->wmask_d, &p->pmask_d, &p->flag_d, &p->jtile_d, &p->jmask_d,
-                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->grp_blk_d, &p->grp_nblk_d, &p->a_rows_d,
+                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->grp_blk_d, &p->grp_nblk_d, &p->a_rows_d, &p->sa4_d, &p->sb4_d, &p->tile4_d, &p->grp4_d, &p->ngrp4_d,
                     &p->own_ws};
   for (DevBuf* b : bufs) dev_free(b);
 }
@@ -1356,6 +1394,28 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     *n_ent = (long long)p->n_tiles_j * 256;
     n_chunks = p->n_chunks_j;
     *ent = (const int*)p->ent_j_d.p;
+  } else if (p->order == 4 && p->prec == POLYSPEC_SPLIT_FP16 && p->n_blk <= ps::kMaxBlkHost) {
+    ps::Ctr4Params cp;
+    cp.D = p->D;
+    cp.absmax = p->absmax;
+    cp.pair_uv = (const int*)p->pairs_d.p;
+    cp.slot_a = (const int*)p->sa4_d.p;
+    cp.slot_b = (const int*)p->sb4_d.p;
+    cp.slot_tile = (const int*)p->tile4_d.p;
+    cp.grp_blk = (const int*)p->grp4_d.p;
+    cp.grp_nblk = (const int*)p->ngrp4_d.p;
+    cp.partials = p->partials;
+    cp.G = launch_points(p);
+    cp.n_shells = p->nb;
+    cp.n_blk = p->n_blk;
+    cp.n_tiles = p->n_tiles;
+    cp.ksteps = p->ksteps;
+    cp.n_chunks = p->n_chunks;
+    cp.wide = p->wide4;
+    PS_TIMED(p, POLYSPEC_PH_CONTRACT, ps::launch_contract_pairs(cp, p->n_groups4, p->batch, st));
+    *n_ent = (long long)p->n_tiles * 256;
+    n_chunks = p->n_chunks;
+    *ent = (const int*)p->ent_d.p;
   } else {
     ps::CtrParams cp;
     cp.D = p->D;
@@ -1363,7 +1423,6 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     cp.slot_uni = (const int*)p->slots_d.p;
     cp.slot_lane = (const int*)p->slot_lane_d.p;
     cp.slot_tile = (const int*)p->slot_tile_d.p;
-    cp.slot_blk = (const int*)p->slot_blk_d.p;
     cp.absmax = p->absmax;
     cp.partials = p->partials;
     cp.G = launch_points(p);
@@ -1373,14 +1432,8 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     cp.n_tiles = p->n_tiles;
     cp.ksteps = p->ksteps;
     cp.n_chunks = p->n_chunks;
-    // order 4 in split FP16: every pair operand formed once per K-step, shared through LDS
-    // (with more pair blocks than fit, each tile group's own blocks)
-    const int npb = p->n_pairs_padded / 16;
-    const bool plds = p->order == 4 && p->prec == POLYSPEC_SPLIT_FP16 && p->n_blk <= 4;
-    cp.n_pair_blocks = !plds ? 0 : p->pair_groups ? ps::kMaxPairBlocksHost : npb;
-    const bool grp = p->order >= 5 || (plds && p->pair_groups);
-    cp.grp_blk = grp ? (const int*)p->grp_blk_d.p : nullptr;
-    cp.grp_nblk = grp ? (const int*)p->grp_nblk_d.p : nullptr;
+    cp.grp_blk = (const int*)p->grp_blk_d.p;
+    cp.grp_nblk = (const int*)p->grp_nblk_d.p;
     cp.a_rows = (const int*)p->a_rows_d.p;
     PS_TIMED(p, POLYSPEC_PH_CONTRACT, ps::launch_contract(p->prec, p->order, cp, p->n_groups, p->batch, st));
     *n_ent = (long long)p->n_tiles * 256;
