@@ -259,11 +259,10 @@ def main():
     # algorithmic flops per launch: 2 per (closing triplet x point) + 1 per (pair x point)
     # for the contraction; 2 per (adjoint weight x point) + 1 per (pair x point) for the
     # adjoint product, whatever the tiles the kernels actually issue
-    # the contraction kernel by order, precision and shells (order 3 in FP32 and BF16 takes the
-    # aligned products where they have fewer tiles)
+    # the contraction kernel by order, precision and shells
     ctr_kernel = ("contract_rows" if order >= 5 else
                   "contract_pairs" if order == 4 and args.precision == "fp16" and nb <= 64 else
-                  "contract_j3" if order == 3 and nb <= 64 and (args.precision == "fp16" or nb <= 16 or nb >= 45) else
+                  "contract_j3" if order == 3 and nb <= (64 if args.precision == "fp16" else 16) else
                   "contract_tiles")
     # algorithmic flops: 2 per (closing tuple x point), plus the row products formed once
     # per point: 1 per pair (orders 3 to 5) and 2 per triple (orders 5 and 6)

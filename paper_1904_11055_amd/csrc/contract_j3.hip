@@ -3,7 +3,7 @@
 namespace ps {
 
 // ---------------------------------------------------------------------------
-// Order 3, products aligned to shell blocks (up to 64 shells, every precision).
+// Order 3, products aligned to shell blocks (FP16: up to 64 shells; FP32, BF16: up to 16).
 //   S[i, j, k] = sum_x d_i d_j d_k, i <= j <= k, by the 16-shell block jb of the middle shell.
 // Every 16 x 16 tile is a product operand (16 rows d_p d_j) times the plain operand of a
 // shell block held in registers.  What fixes the rows of the product operand:
@@ -37,10 +37,9 @@ static_assert(kSlots == kSlotsHost && kSlots4 == kSlots4Host && kSlotsMax == kSl
 // barrier.  What is left: without staging 28 ms, without forming products 29.7, the matrix
 // products alone 20.  128^3 x 8, 24 shells: 1.99 -> 0.98 ms.
 //
-// FP16 forms the products from the split words; FP32 and BF16 from float32 values, which
-// BF16 splits afterwards, as the pair tiles of contract_tiles do (the plan chooses between
-// the two).  512^3, 64 shells: BF16 63.2 -> 40.8 ms, FP32 119 -> 99.7; 256^3, 53 shells:
-// BF16 5.99 -> 5.17.
+// FP16 forms the products from the split words; FP32 and BF16, on plans of one block, from
+// float32 values, which BF16 splits afterwards, as the pair tiles of contract_tiles do.
+// 256^3, 13 shells, FP32: 0.89 -> 0.75 ms.
 template <int PREC, int NBLK, bool ALL>
 __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
   // [buffer][K-step][shell block][lane]: the operand's 16-byte words, FP16 hi and lo, else
@@ -232,18 +231,18 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
 hipError_t launch_contract_j3(int prec, const CtrJParams& p, int batch, hipStream_t st) {
   dim3 grid(p.n_chunks, 1, batch);
 #define L(PREC, NBLK, ALL) hipLaunchKernelGGL((contract_j3<PREC, NBLK, ALL>), grid, dim3(kJThreads), 0, st, p)
-#define BY_BLOCKS(PREC)                                                       \
-  switch (p.n_blk) {                                                          \
-    case 1: L(PREC, 1, false); break;                                         \
-    case 2: L(PREC, 2, false); break;                                         \
-    case 3: if (p.all_used) L(PREC, 3, true); else L(PREC, 3, false); break;  \
-    case 4: if (p.all_used) L(PREC, 4, true); else L(PREC, 4, false); break;  \
-    default: return hipErrorInvalidValue;                                     \
+  if (prec != kFP16) {
+    if (p.n_blk != 1) return hipErrorInvalidValue;
+    if (prec == kFP32) L(kFP32, 1, false); else L(kBF16, 1, false);
+    return hipGetLastError();
   }
-  if (prec == kFP32) BY_BLOCKS(kFP32)
-  else if (prec == kBF16) BY_BLOCKS(kBF16)
-  else BY_BLOCKS(kFP16)
-#undef BY_BLOCKS
+  switch (p.n_blk) {
+    case 1: L(kFP16, 1, false); break;
+    case 2: L(kFP16, 2, false); break;
+    case 3: if (p.all_used) L(kFP16, 3, true); else L(kFP16, 3, false); break;
+    case 4: if (p.all_used) L(kFP16, 4, true); else L(kFP16, 4, false); break;
+    default: return hipErrorInvalidValue;
+  }
 #undef L
   return hipGetLastError();
 }
