@@ -4,6 +4,25 @@
 
 namespace ps {
 
+// Sum over rows r0 <= r < r1 of src[r * stride], in order.  One thread per entry leaves few loads
+// in flight on the small plans, so 32 rows (8 of FP64) are loaded before the first is added (64^3, 2
+// tiles: 19 -> 6 us; 512^3, 186 tiles: 0.42 -> 0.29 ms).
+template <typename T>
+__device__ __forceinline__ double sum_rows(const T* __restrict__ src, size_t stride, int r0, int r1) {
+  constexpr int kAhead = sizeof(T) == 8 ? 8 : 32;
+  double s = 0.0;
+  for (; r0 + kAhead <= r1; r0 += kAhead) {
+    T v[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) v[k] = src[(size_t)(r0 + k) * stride];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) s += (double)v[k];
+  }
+#pragma unroll 4
+  for (; r0 < r1; ++r0) s += (double)src[(size_t)r0 * stride];
+  return s;
+}
+
 // level 1: tmp[b][grp][e] = sum_{c in grp} part[b][c][e], or += when accumulating
 // over the slabs of a streamed contraction.  With `closing_of_entry` (streamed plans
 // whose operands were scaled by the slab's own maxima) the sum of an entry is unscaled
@@ -20,8 +39,7 @@ __global__ void reduce_chunks_f32(const float* __restrict__ part, double* __rest
   const int c0 = grp * chunks_per_group;
   const int c1 = min(n_chunks, c0 + chunks_per_group);
   const float* src = part + (size_t)b * n_chunks * n_ent;
-  double s = 0.0;
-  for (int c = c0; c < c1; ++c) s += (double)src[(size_t)c * n_ent + e];
+  double s = sum_rows(src + e, n_ent, c0, c1);
   if (closing_of_entry != nullptr) {
     const int t = closing_of_entry[e];
     s = t < 0 ? 0.0 : ldexp(s, tuple_unscale_exp(absmax, b, n_shells, bins, t, order, prec));
@@ -39,8 +57,7 @@ __global__ void reduce_chunks_f64(const double* __restrict__ part, double* __res
   const int c0 = grp * chunks_per_group;
   const int c1 = min(n_chunks, c0 + chunks_per_group);
   const double* src = part + (size_t)b * n_chunks * n_ent;
-  double s = 0.0;
-  for (int c = c0; c < c1; ++c) s += src[(size_t)c * n_ent + e];
+  const double s = sum_rows(src + e, n_ent, c0, c1);
   tmp[((size_t)b * n_groups + grp) * n_ent + e] = s;
 }
 
@@ -56,8 +73,7 @@ __global__ void gather_normalize(const double* __restrict__ tmp, int n_groups, l
   if (t >= n_closing) return;
   const long long e = ent_idx[t];
   const double* src = tmp + (size_t)b * n_groups * n_ent;
-  double s = 0.0;
-  for (int grp = 0; grp < n_groups; ++grp) s += src[(size_t)grp * n_ent + e];
+  double s = sum_rows(src + e, n_ent, 0, n_groups);
   // the scaling of the contraction's operands (absmax is null when the reduction has
   // already removed it)
   if (absmax != nullptr && (prec == kFP16 || order >= 5))
