@@ -52,12 +52,14 @@ constexpr size_t sym_lds_bytes() {
 // They start the accumulators, which costs no register.
 template <int PREC, int KB, int ORDER>
 __device__ __forceinline__ void sym_equal(float (&acc)[kAdjPB][KB][8], const AdjFields<PREC, KB>& f,
-                                          const Operand<PREC> (&fop)[kAdjPB][KB], const float2* equal, int hh) {
+                                          const Operand<PREC> (&fop)[kAdjPB][KB], const float2* __restrict__ equal,
+                                          int n_shells, int hh) {
 #pragma unroll
   for (int M = 0; M < KB; ++M)
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      const float2 w = equal[16 * M + 8 * hh + r];
+      const int k = 16 * M + 8 * hh + r;
+      const float2 w = k < n_shells ? equal[k] : make_float2(0.f, 0.f);
 #pragma unroll
       for (int pb = 0; pb < kAdjPB; ++pb) {
         const float x = f.F[pb][M][r];
@@ -147,8 +149,6 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
   const float* Db = D + (size_t)b * n_shells * G;
   const uint4* Wb = W + (size_t)b * sym_base((n_shells + 15) / 16) * kSymBlockWords;
 
-  __shared__ float2 eqs[16 * KB];
-  if (tid < 16 * KB) eqs[tid] = tid < n_shells ? equal[b * 64 + tid] : make_float2(0.f, 0.f);
   AdjFields<PREC, KB> f;
   adj_load_fields<PREC, KB>(f, Db, G, xw, hh, n_shells, nullptr, b);
 #pragma unroll
@@ -160,9 +160,9 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
     for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
 
   float acc[kAdjPB][KB][8];
+  sym_equal<PREC, KB, 3>(acc, f, fop, equal + b * 64, n_shells, hh);
   const float half_of[2] = {hh == 0 ? 0.5f : 0.f, hh == 1 ? 0.5f : 0.f};
   __syncthreads();
-  sym_equal<PREC, KB, 3>(acc, f, fop, eqs, hh);
 
   // One stage: copy the next one in, then the pairs of this one.  The two buffers are
   // restrict parameters so that the compiler knows the reads of `now` not to touch the
@@ -282,8 +282,6 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
   const int n_words = sym4_blocks(n_shells) * kSymBlockWords;
   const uint4* Wb = W + (size_t)b * n_words;
 
-  __shared__ float2 eqs[16 * KB];
-  if (tid < 16 * KB) eqs[tid] = tid < n_shells ? equal[b * 64 + tid] : make_float2(0.f, 0.f);
   AdjFields<PREC, KB> f;
   adj_load_fields<PREC, KB>(f, Db, G, xw, hh, n_shells, nullptr, b);
 #pragma unroll
@@ -297,13 +295,13 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
 #pragma unroll
     for (int uc = 0; uc < KB; ++uc) fop[pb][uc] = make_operand<PREC>(f.F[pb][uc], 1.f);
   float acc[kAdjPB][KB][8];
+  sym_equal<PREC, KB, 4>(acc, f, fop, equal + b * 64, n_shells, hh);
   // d_l at the lane's points and the mask of l, one l ahead
   float dl_next[kAdjPB];
 #pragma unroll
   for (int pb = 0; pb < kAdjPB; ++pb) dl_next[pb] = Db[xw + 32 * pb];
   int pm_next = pmask[0];
   __syncthreads();
-  sym_equal<PREC, KB, 4>(acc, f, fop, eqs, hh);
 
   float dl[kAdjPB], al[kAdjPB];
   unsigned pm = 0;
