@@ -126,8 +126,8 @@ __device__ __forceinline__ void sym_add(float (&acc)[kAdjPB][KB][8], float (&q)[
 // stage is copied from global memory straight into LDS while one is in use.  dense: the
 // plan aliases, so no block is empty by the triangle bound.
 //
-// 512^3, 64 unit shells, BF16: 92.3 ms with every m and a_m = sum_v d_v Y_v, 72.3 ms in
-// this form (1.2 PFLOP/s issued); 128^3 x 8, 24 shells: 2.97 -> 2.01 ms.  What is left at
+// 512^3, 64 unit shells, BF16: 92.3 ms with every m and a_m = sum_v d_v Y_v, 76.0 ms in
+// this form (1.15 PFLOP/s issued); 128^3 x 8, 24 shells: 2.97 -> 2.19 ms.  What is left at
 // 512^3: the row transform takes 8 ms, weight copies and barriers 1.5, the q products 6; the
 // matrix products alone take about 52 ms at the 1.65 PFLOP/s that the power limit leaves
 // for random operands.  16 waves of one column block each: 77.8 ms (before the row
@@ -259,8 +259,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
 // pmask: per l, the pairs of partners that hold a weight (bit k / 2).  Stages are those of
 // order 3, for every l in turn; a pair's blocks are stored for k / 2 <= l / 2 only.
 //
-// BF16, 256^3, against a_m = sum d_v d_w Y over every m: 14.8 -> 11.1 ms with 24 shells of
-// width 2, 85.9 -> 39.8 ms with 40 unit shells, where the last shell blocks hold most of
+// BF16, 256^3, against a_m = sum d_v d_w Y over every m: 14.8 -> 11.6 ms with 24 shells of
+// width 2, 85.9 -> 40.7 ms with 40 unit shells, where the last shell blocks hold most of
 // the products and a corner of k x k replaces 64 rows x every chunk.
 template <int PREC, int NF, int KB>
 __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __restrict__ D, const uint4* __restrict__ W,
