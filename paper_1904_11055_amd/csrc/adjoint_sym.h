@@ -161,7 +161,6 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
 
   float acc[kAdjPB][KB][8];
   sym_equal<PREC, KB, 3>(acc, f, fop, equal + b * 64, n_shells, hh);
-  const float half_of[2] = {hh == 0 ? 0.5f : 0.f, hh == 1 ? 0.5f : 0.f};
   __syncthreads();
 
   // One stage: copy the next one in, then the pairs of this one.  The two buffers are
@@ -218,7 +217,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
           });
         }
       }
-      // a_k += (1/2) sum_m d_m Y_k[m], in the lane half that holds shell k
+      // a_k += (1/2) sum_m d_m Y_k[m], in the lane half that holds shell k (selected, not
+      // multiplied by 0 in the other half: the sum may be infinite or NaN)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
           const auto sw = __builtin_amdgcn_permlane32_swap(own, own, false, false);
           const float tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
           float& a = acc[pb][kb][(kk + t) % 8];
-          a = fmaf(half_of[(kk + t) / 8], tot, a);
+          a = fmaf(0.5f, hh == (kk + t) / 8 ? tot : 0.f, a);
         }
     });
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's part of the next stage is in LDS
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
             const auto sw = __builtin_amdgcn_permlane32_swap(own, own, false, false);
             const float tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
             float& a = acc[pb][kb][(kk + t) % 8];
-            a = fmaf(hh == (kk + t) / 8 ? 0.5f * dl[pb] : 0.f, tot, a);
+            a = hh == (kk + t) / 8 ? fmaf(0.5f * dl[pb], tot, a) : a;
           }
       });
     }
@@ -436,9 +436,9 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
     for (int M = 0; M < KB; ++M)
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
-        const float here = (l >> 4 == M && (l & 7) == r) ? 1.f : 0.f;   // uniform: no indexed registers
+        const bool here = l >> 4 == M && (l & 7) == r;   // uniform: no indexed registers
 #pragma unroll
-        for (int pb = 0; pb < kAdjPB; ++pb) acc[pb][M][r] = fmaf(here, al[pb], acc[pb][M][r]);
+        for (int pb = 0; pb < kAdjPB; ++pb) acc[pb][M][r] += here ? al[pb] : 0.f;
       }
     base += sym4_blocks_of(l) * kSymBlockWords;
   }
