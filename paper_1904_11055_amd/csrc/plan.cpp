@@ -116,12 +116,17 @@ struct polyspec_plan_s {
   DevBuf tw32, shell_q, qmax_d, pairs_d, slots_d, slot_lane_d, slot_tile_d, ent_d, bins_d, fnorm_d, lookup_d,
       wmask_d, pmask_d, flag_d;
   DevBuf jtile_d, jmask_d, ent_j_d;
-  DevBuf grp_blk_d, grp_nblk_d;   // orders 5 and 6: the A blocks of each tile group
   // order 4 up to 64 shells: the schedule of contract_pairs (FP16)
   int n_groups4 = 0;
   bool wide4 = false;
   DevBuf sa4_d, sb4_d, tile4_d, grp4_d, ngrp4_d;
-  DevBuf a_rows_d;                // orders 5 and 6: staged row offsets of the A rows
+  // orders 5 and 6: staged row offsets of the A rows; tile groups, [1] those of FP32 at order 6
+  struct RowGroups {
+    int n_groups = 0;
+    DevBuf slots, slot_lane, slot_tile, grp_blk, grp_nblk;
+  };
+  DevBuf a_rows_d;
+  RowGroups row_groups[2];
   DevBuf closing_of_ent_d, closing_of_ent_j_d;   // streamed plans: tile entry -> closing tuple (or -1)
   // workspace carving
   DevBuf own_ws;
@@ -448,9 +453,14 @@ void build_triples(const polyspec_plan_s* p, bool by_largest, std::vector<int>* 
 // Orders 5 and 6: tile groups over ranges of kHiABlocks A blocks (formed once per stage in
 // LDS), each with up to kHiWaves x kHiSlots tiles; the tiles of one B block go to one wave
 // (a unit, cut where a wave has no room), which forms the block once.  A formation costs
-// about four tiles.
+// about four tiles of a split.  In FP32, whose tiles take five times as long, it costs one or
+// less, and at order 6, with up to 11 tiles to a unit, whole units leave the waves uneven.  `fine`
+// cuts them to 3 tiles (128^3, shells of width 1/4, FP32: 12 shells 1.03 -> 0.89 ms, 16 3.03 -> 2.79,
+// 20 8.36 -> 8.04; 256^3, 8 shells 2.37 -> 1.80; the FP16 split, 16 shells: 1.60 -> 1.79).  Order 5
+// has two tiles to a unit and keeps them whole (FP32, 24 shells of width 1/2 at 128^3: 4.33
+// against 4.42 ms).
 polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& tlist, const std::vector<int>& arows,
-                                const std::vector<int>& brows) {
+                                const std::vector<int>& brows, bool fine) {
   const int S = ps::kSlotsMaxHost, W = ps::kHiWaves, cap = ps::kHiSlots;
   std::map<std::pair<int, int>, std::vector<int>> unit_of;   // (A range, B block) -> tiles
   for (size_t t = 0; t < tlist.size(); ++t) unit_of[{tlist[t].a / ps::kHiABlocks, tlist[t].b}].push_back((int)t);
@@ -465,10 +475,14 @@ polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& 
   };
   std::vector<Group> groups;
   std::map<int, std::vector<std::vector<int>>> by_range;
-  for (const auto& kv : unit_of)
-    for (size_t f = 0; f < kv.second.size(); f += cap)
-      by_range[kv.first.first].push_back({kv.second.begin() + f,
-                                          kv.second.begin() + std::min(kv.second.size(), f + (size_t)cap)});
+  const size_t most = fine ? 3 : cap;
+  const double form_cost = fine ? 1.0 : 4.0;
+  for (const auto& kv : unit_of) {
+    const std::vector<int>& tl = kv.second;
+    const size_t pieces = (tl.size() + most - 1) / most, per = (tl.size() + pieces - 1) / pieces;
+    for (size_t f = 0; f < tl.size(); f += per)
+      by_range[kv.first.first].push_back({tl.begin() + f, tl.begin() + std::min(tl.size(), f + per)});
+  }
   for (auto& kv : by_range) {
     std::stable_sort(kv.second.begin(), kv.second.end(),
                      [](const std::vector<int>& x, const std::vector<int>& y) { return x.size() > y.size(); });
@@ -488,10 +502,11 @@ polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& 
       }
       best->units.push_back(u);
       best->tiles += (int)u.size();
-      best->load += 4.0 + (double)u.size();
+      best->load += form_cost + (double)u.size();
     }
   }
-  p->n_groups = (int)groups.size();
+  polyspec_plan_s::RowGroups& out = p->row_groups[fine];
+  out.n_groups = (int)groups.size();
   // staged row offset of a shell in units of 16 bytes, 10 bits per row of the product
   auto row_word = [](int shells, int fields) {
     int w = 0;
@@ -500,10 +515,10 @@ polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& 
   };
   std::vector<int> a_rows(arows.size());
   for (size_t i = 0; i < arows.size(); ++i) a_rows[i] = row_word(arows[i], p->order == 6 ? 3 : 2);
-  std::vector<int> uni((size_t)p->n_groups * W * (S / 4), 0), lanew((size_t)p->n_groups * W * 16 * S, 0);
-  std::vector<int> slot_tile((size_t)p->n_groups * W * S, -1);
-  std::vector<int> grp_blk((size_t)p->n_groups * ps::kHiABlocks, 0), grp_nblk(p->n_groups, 0);
-  for (int gi = 0; gi < p->n_groups; ++gi) {
+  std::vector<int> uni((size_t)out.n_groups * W * (S / 4), 0), lanew((size_t)out.n_groups * W * 16 * S, 0);
+  std::vector<int> slot_tile((size_t)out.n_groups * W * S, -1);
+  std::vector<int> grp_blk((size_t)out.n_groups * ps::kHiABlocks, 0), grp_nblk(out.n_groups, 0);
+  for (int gi = 0; gi < out.n_groups; ++gi) {
     std::vector<int> blocks;
     for (const Wave& w : groups[gi].waves)
       for (const auto& u : w.units)
@@ -527,12 +542,12 @@ polyspec_status pack_high_order(polyspec_plan_s* p, const std::vector<TileKey>& 
       for (; s < S; ++s) uni[gw * (S / 4) + s / 4] |= 0x80 << (8 * (s % 4));
     }
   }
-  PS_TRY(upload(p, &p->slots_d, uni));
-  PS_TRY(upload(p, &p->slot_lane_d, lanew));
-  PS_TRY(upload(p, &p->slot_tile_d, slot_tile));
-  PS_TRY(upload(p, &p->a_rows_d, a_rows));
-  PS_TRY(upload(p, &p->grp_blk_d, grp_blk));
-  PS_TRY(upload(p, &p->grp_nblk_d, grp_nblk));
+  PS_TRY(upload(p, &out.slots, uni));
+  PS_TRY(upload(p, &out.slot_lane, lanew));
+  PS_TRY(upload(p, &out.slot_tile, slot_tile));
+  PS_TRY(upload(p, &out.grp_blk, grp_blk));
+  PS_TRY(upload(p, &out.grp_nblk, grp_nblk));
+  if (!fine) PS_TRY(upload(p, &p->a_rows_d, a_rows));
   return POLYSPEC_OK;
 }
 
@@ -682,7 +697,10 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
     const int t = tiles[TileKey{loc[c][0], loc[c][1]}];
     (*ent_of_cand)[c] = t * 256 + tile_entry(loc[c][2], loc[c][3]);
   }
-  if (n >= 5) return pack_high_order(p, tlist, arows, brows);
+  if (n >= 5) {
+    if (n == 6) PS_TRY(pack_high_order(p, tlist, arows, brows, true));
+    return pack_high_order(p, tlist, arows, brows, false);
+  }
   // units: runs of tiles sharing the A block, cut into pieces that fit one wave
   const int cap = n == 2   ? ps::kSlots2Host
                   : n == 3 ? ps::kSlotsHost
@@ -1177,9 +1195,11 @@ void release(polyspec_plan_s* p) {
   p->ev_pool.clear();
   DevBuf* bufs[] = {&p->tw32, &p->shell_q, &p->qmax_d, &p->pairs_d, &p->slots_d, &p->slot_lane_d, &p->slot_tile_d,   &p->ent_d,
                     &p->bins_d, &p->fnorm_d, &p->lookup_d, &p->wmask_d, &p->pmask_d, &p->flag_d, &p->jtile_d, &p->jmask_d,
-                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->grp_blk_d, &p->grp_nblk_d, &p->a_rows_d, &p->sa4_d, &p->sb4_d, &p->tile4_d, &p->grp4_d, &p->ngrp4_d,
+                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->a_rows_d, &p->sa4_d, &p->sb4_d, &p->tile4_d, &p->grp4_d, &p->ngrp4_d,
                     &p->own_ws};
   for (DevBuf* b : bufs) dev_free(b);
+  for (auto& r : p->row_groups)
+    for (DevBuf* b : {&r.slots, &r.slot_lane, &r.slot_tile, &r.grp_blk, &r.grp_nblk}) dev_free(b);
 }
 
 }  // namespace
@@ -1420,9 +1440,11 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     ps::CtrParams cp;
     cp.D = p->D;
     cp.pair_uv = (const int*)p->pairs_d.p;
-    cp.slot_uni = (const int*)p->slots_d.p;
-    cp.slot_lane = (const int*)p->slot_lane_d.p;
-    cp.slot_tile = (const int*)p->slot_tile_d.p;
+    const auto& rows = p->row_groups[p->order == 6 && p->prec == POLYSPEC_FP32];
+    const bool hi = p->order >= 5;
+    cp.slot_uni = (const int*)(hi ? rows.slots : p->slots_d).p;
+    cp.slot_lane = (const int*)(hi ? rows.slot_lane : p->slot_lane_d).p;
+    cp.slot_tile = (const int*)(hi ? rows.slot_tile : p->slot_tile_d).p;
     cp.absmax = p->absmax;
     cp.partials = p->partials;
     cp.G = launch_points(p);
@@ -1432,10 +1454,11 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     cp.n_tiles = p->n_tiles;
     cp.ksteps = p->ksteps;
     cp.n_chunks = p->n_chunks;
-    cp.grp_blk = (const int*)p->grp_blk_d.p;
-    cp.grp_nblk = (const int*)p->grp_nblk_d.p;
+    cp.grp_blk = (const int*)rows.grp_blk.p;
+    cp.grp_nblk = (const int*)rows.grp_nblk.p;
     cp.a_rows = (const int*)p->a_rows_d.p;
-    PS_TIMED(p, POLYSPEC_PH_CONTRACT, ps::launch_contract(p->prec, p->order, cp, p->n_groups, p->batch, st));
+    PS_TIMED(p, POLYSPEC_PH_CONTRACT, ps::launch_contract(p->prec, p->order, cp, hi ? rows.n_groups : p->n_groups,
+                                                               p->batch, st));
     *n_ent = (long long)p->n_tiles * 256;
     n_chunks = p->n_chunks;
     *ent = (const int*)p->ent_d.p;
