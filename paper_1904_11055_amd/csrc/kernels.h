@@ -109,6 +109,13 @@ constexpr int kJLow = 14;      // j = 16 + w + 8 q, i in block 0: slots 3 q + co
 constexpr int kJHigh = 20;     // j = 32 + w + 8 q, k in block 3: slots 3 q + columns i of blocks 0..2
 constexpr int kJShared = 26;   // the half-full shells of blocks 0, 1 (waves 0, 1) and 2, 3 (waves 2, 3)
 constexpr int kJSlots = 28;
+// The slots that contract_j3 multiplies together, by one product operand: `count` shell blocks
+// from `block` on, as far as the plan's go, of plans of at least `plan_blk` blocks.
+struct JGroup { int slot, count, block, plan_blk; };
+constexpr JGroup kJGroups[] = {{kJDiag0, 2, 0, 1}, {kJDiag1, 3, 1, 2}, {kJDiag2, 3, 0, 3}, {kJDiag3, 4, 0, 4},
+                               {kJLow, 2, 1, 2},   {kJLow + 3, 2, 1, 2}, {kJHigh, 3, 0, 4}, {kJHigh + 3, 3, 0, 4}};
+// Slots multiplied alone, for the shell blocks 2 and 3 of the small shells' operands.
+constexpr JGroup kJCorners[] = {{kJDiag0 + 2, 1, 2, 3}, {kJDiag0 + 3, 1, 3, 4}, {kJLow + 2, 1, 3, 4}, {kJLow + 5, 1, 3, 4}};
 struct JPlace {
   int wave, slot, row, col;
 };

@@ -111,13 +111,14 @@ struct polyspec_plan_s {
   std::vector<int> pmask_host;     // order-4 adjoint: per l, the pairs of partners with a weight
   bool jsched = false, j_all_used = false;
   int n_tiles_j = 0, ksteps_j = 0, n_chunks_j = 0;
+  std::vector<unsigned> jmask_host;   // per wave, the slots with a tile
 
   // device tables
   DevBuf tw32, shell_q, qmax_d, pairs_d, slots_d, slot_lane_d, slot_tile_d, ent_d, bins_d, fnorm_d, lookup_d,
       wmask_d, pmask_d, flag_d;
   DevBuf jtile_d, jmask_d, ent_j_d;
   // order 4 up to 64 shells: the schedule of contract_pairs (FP16)
-  int n_groups4 = 0;
+  int n_groups4 = 0, n_issued4 = 0;   // n_issued4: tiles multiplied, those without a tuple among them
   bool wide4 = false;
   DevBuf sa4_d, sb4_d, tile4_d, grp4_d, ngrp4_d;
   // orders 5 and 6: staged row offsets of the A rows; tile groups, [1] those of FP32 at order 6
@@ -629,6 +630,8 @@ polyspec_status pack_order4(polyspec_plan_s* p, const std::vector<TileKey>& tlis
           sa[at] |= local(T * sl.first.first + a) << (8 * a);
           tile[at * T + a] = sl.second[a];
         }
+        // a slot of two is multiplied as a whole, one of four by halves
+        p->n_issued4 += T == 2 ? 2 : 2 * ((sl.second[0] >= 0 || sl.second[1] >= 0) + (sl.second[2] >= 0 || sl.second[3] >= 0));
         sb[at] = local(sl.first.second) | (load ? 0x100 : 0) | (sl.second[0] >= 0 || sl.second[1] >= 0 ? 0x200 : 0) |
                  (sl.second[2] >= 0 || sl.second[3] >= 0 ? 0x400 : 0);
       }
@@ -784,6 +787,33 @@ polyspec_status build_tiles(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
   return POLYSPEC_OK;
 }
 
+// The tiles of a group that a wave's slot mask holds, and how many slots the plan's blocks give it.
+int j_count(const ps::JGroup& g, int n_blk) { return std::max(0, std::min(g.count, n_blk - g.block)); }
+unsigned j_bits(unsigned mask, const ps::JGroup& g, int n_blk) {
+  return mask >> g.slot & ((1u << j_count(g, n_blk)) - 1);
+}
+
+// Tiles that contract_j3 multiplies: a group with a tile as a whole (in FP32 only the tiles),
+// with j_all_used every group, and the corners tile by tile.
+int j_issued(const polyspec_plan_s* p) {
+  int n = 0;
+  const bool all = p->j_all_used && p->prec == POLYSPEC_SPLIT_FP16;
+  auto add = [&](unsigned mask, const ps::JGroup& g) {
+    const unsigned bits = j_bits(mask, g, p->n_blk);
+    if (p->prec == POLYSPEC_FP32) n += __builtin_popcount(bits);
+    else if (all || bits) n += j_count(g, p->n_blk);
+  };
+  for (int w = 0; w < ps::kJWaves; ++w) {
+    const unsigned mask = p->jmask_host[w];
+    for (const ps::JGroup& g : ps::kJGroups)
+      if (p->n_blk >= g.plan_blk) add(mask, g);
+    for (const ps::JGroup& g : ps::kJCorners)
+      if (p->n_blk >= g.plan_blk) n += __builtin_popcount(j_bits(mask, g, p->n_blk));
+    if (mask >> ps::kJShared) add(mask, {ps::kJShared, 2, w & 1 ? 2 : 0, 1});
+  }
+  return n;
+}
+
 // Order 3, shell-block aligned schedule: candidate (i <= j <= k) lives in the wave, slot and
 // tile entry of jplace(); used slots get compact tile ids.
 polyspec_status build_jsched(polyspec_plan_s* p, std::vector<int>* ent_of_cand) {
@@ -806,15 +836,12 @@ polyspec_status build_jsched(polyspec_plan_s* p, std::vector<int>* ent_of_cand) 
       mask[w] |= 1u << s;
     }
   p->n_tiles_j = id;
-  // slots of each kind (the corners of contract_j3 left out), as far as the plan's blocks go
-  p->j_all_used = true;
-  for (int w = 0; w < ps::kJWaves; ++w) {
-    const unsigned kinds[] = {0x3u << ps::kJDiag0, 0x7u << ps::kJDiag1, 0x3u << ps::kJLow, 0x3u << (ps::kJLow + 3),
-                              0x7u << ps::kJDiag2, 0xfu << ps::kJDiag3, 0x7u << ps::kJHigh,
-                              0x7u << (ps::kJHigh + 3)};
-    const int n_kinds = p->n_blk == 4 ? 8 : p->n_blk == 3 ? 5 : p->n_blk == 2 ? 4 : 1;
-    for (int k = 0; k < n_kinds; ++k) p->j_all_used = p->j_all_used && (mask[w] & kinds[k]) != 0;
-  }
+  // FP16 of three and four blocks: whether every wave has a tile of every group
+  p->j_all_used = p->n_blk >= 3;
+  for (int w = 0; w < ps::kJWaves; ++w)
+    for (const ps::JGroup& g : ps::kJGroups)
+      if (p->n_blk >= g.plan_blk && j_bits(mask[w], g, p->n_blk) == 0) p->j_all_used = false;
+  p->jmask_host = mask;
   ent_of_cand->resize(nc);
   for (size_t c = 0; c < nc; ++c) {
     const ps::JPlace w = place(c);
@@ -1389,6 +1416,11 @@ static bool uses_j3(const polyspec_plan_s* p) {
   return p->prec == POLYSPEC_SPLIT_FP16 || (p->n_blk == 1 && p->ksteps_j == p->ksteps);
 }
 
+// Whether an order-4 plan contracts by contract_pairs.
+static bool uses_pairs(const polyspec_plan_s* p) {
+  return p->order == 4 && p->prec == POLYSPEC_SPLIT_FP16 && p->n_blk <= ps::kMaxBlkHost;
+}
+
 // One contraction launch over the fields in D (the whole grid or one slab) and its
 // FP64 reduction over chunks into p->red, added to what is there when `accumulate`.
 // Returns the tile entries and entry table that the gather needs.
@@ -1414,7 +1446,7 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     *n_ent = (long long)p->n_tiles_j * 256;
     n_chunks = p->n_chunks_j;
     *ent = (const int*)p->ent_j_d.p;
-  } else if (p->order == 4 && p->prec == POLYSPEC_SPLIT_FP16 && p->n_blk <= ps::kMaxBlkHost) {
+  } else if (uses_pairs(p)) {
     ps::Ctr4Params cp;
     cp.D = p->D;
     cp.absmax = p->absmax;
@@ -1728,7 +1760,7 @@ polyspec_status polyspec_issued_flops(polyspec_plan_t p, int32_t phase, double* 
   *flops = 0.0;
   if (phase == POLYSPEC_PH_CONTRACT) {
     // a 16 x 16 tile is 2 * 256 flops per grid point and product term
-    *flops = (uses_j3(p) ? p->n_tiles_j : p->n_tiles) * 512.0 * terms * pts;
+    *flops = (uses_j3(p) ? j_issued(p) : uses_pairs(p) ? p->n_issued4 : p->n_tiles) * 512.0 * terms * pts;
   } else if (phase == POLYSPEC_PH_ADJ_GEMM && p->order == 4 && p->nb <= ps::kAdj4MaxShells) {
     // 32 x 32 x 16 products per 32 grid points.  FP16: per item (w, v) the 16-shell chunks
     // of u <= v, for each 32-row block of m with a weight (the only block up to 32
