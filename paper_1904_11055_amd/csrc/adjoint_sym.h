@@ -23,10 +23,7 @@
 
 namespace ps {
 
-constexpr int kSymBlockWords = 2 * 64;   // hi and lo words of a block's 64 lanes
-__host__ __device__ constexpr int sym_stage_words(int kb) { return sym_stage_pairs(kb) * sym_blocks(kb) * kSymBlockWords; }
-// Copies of one word per thread that a stage takes.
-__host__ __device__ constexpr int sym_rounds(int kb) { return (sym_stage_words(kb) + kAdjThreads - 1) / kAdjThreads; }
+static_assert(kAdjThreads == kSymCopyWords, "a round copies one word per thread");
 template <int KB>
 constexpr int sym_buffer_words() {
   int r = 0;

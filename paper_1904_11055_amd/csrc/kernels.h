@@ -189,6 +189,22 @@ __host__ __device__ constexpr int sym_base(int kb) {
   return n;
 }
 
+constexpr int kSymBlockWords = 2 * 64;   // 16-byte words of a block: hi and lo of its 64 lanes
+constexpr int kSymCopyWords = 512;       // one word per thread: a stage is copied in whole rounds
+__host__ __device__ constexpr int sym_stage_words(int kb) { return sym_stage_pairs(kb) * sym_blocks(kb) * kSymBlockWords; }
+__host__ __device__ constexpr int sym_rounds(int kb) { return (sym_stage_words(kb) + kSymCopyWords - 1) / kSymCopyWords; }
+// Weight words of one batch entry of order 3, and of what the last round of a stage reads past
+// its end (the stages of block 2, 18 blocks of 128 words in five rounds).
+__host__ __device__ constexpr int sym_words(int n_shells) { return sym_base((n_shells + 15) / 16) * kSymBlockWords; }
+__host__ __device__ constexpr int sym_words_past(int n_shells) {
+  int r = 0;
+  for (int kb = 0; 16 * kb < n_shells; ++kb) {
+    const int n = sym_rounds(kb) * kSymCopyWords - sym_stage_words(kb);
+    r = n > r ? n : r;
+  }
+  return r;
+}
+
 // Position of a block within its pair: the S chains first (uc ascending), then the P
 // chains from the largest uc down, the blocks that the triangle bound empties last, so
 // that the others are contiguous.

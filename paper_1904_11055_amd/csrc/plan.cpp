@@ -337,10 +337,16 @@ WsLayout layout_of(const polyspec_plan_s* p) {
   L.partials = align256((size_t)p->batch * p->n_chunks * tiles * 256 * sizeof(float));
   L.red = align256((size_t)p->batch * p->red_groups * tiles * 256 * sizeof(double));
   L.absmax = align256(zf * sizeof(unsigned)) + align256(zf * ps::kAbsmaxSpreadHost * sizeof(unsigned));
-  L.W = !adjoint ? 0
-        : p->order == 3 ? align256((size_t)p->batch * p->nb * 4 * 2 * 2 * 64 * 16)
-        : adjoint ? align256((size_t)p->batch * (p->nb * (p->nb + 1) / 2) * ps::adj4_words_per_item(p->nb) * 16)
-                  : 0;
+  // weight words, whichever precision the adjoint runs in: the FP16 layout or the symmetric form
+  // (whose order-4 copies are clamped to the entry)
+  if (adjoint) {
+    const size_t b = p->batch, nb = p->nb;
+    const size_t words = p->order == 3
+                             ? std::max(b * nb * 1024, b * ps::sym_words(p->nb) + ps::sym_words_past(p->nb))
+                             : b * std::max(nb * (nb + 1) / 2 * ps::adj4_words_per_item(p->nb),
+                                            (size_t)ps::sym4_blocks(p->nb) * ps::kSymBlockWords);
+    L.W = align256(words * 16);
+  }
   L.rowmax = adjoint ? align256((size_t)p->batch * 64 * sizeof(unsigned long long)) : 0;
   L.total = L.box + L.gbox + L.H1 + L.H1a + L.H2 + L.D + L.A + L.partials + L.red + L.absmax + L.W + L.rowmax;
   return L;
