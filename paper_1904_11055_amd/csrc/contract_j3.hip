@@ -42,6 +42,7 @@ static_assert(kSlots == kSlotsHost && kSlots4 == kSlots4Host && kSlotsMax == kSl
 // 256^3, 13 shells, FP32: 0.89 -> 0.75 ms.
 template <int PREC, int NBLK, bool ALL>
 __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
+  static_assert(PREC == kFP16 || (NBLK == 1 && !ALL), "FP32 and BF16: plans of one block");
   // [buffer][K-step][shell block][lane]: the operand's 16-byte words, FP16 hi and lo, else
   // the float32 values 0..3 and 4..7; BF16 keeps the split words beside them
   __shared__ uint4 opHi[2][2][kMaxBlk][64];
@@ -157,11 +158,6 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
         else
           Bop[kb] = words(64 * kb + my_slot);
       }
-      // a plain block as a factor of a product
-      auto plain = [&](auto kc) {
-        if constexpr (PREC == kBF16) return words(64 * decltype(kc)::value + my_slot);
-        else return Bop[decltype(kc)::value];
-      };
       // Slots s0 .. s0 + CNT - 1: the product operand times the blocks x0, x0 + 1, ... of the
       // plan, the products of the split in turn, so that none waits for the one before it.
       auto tiles = [&](auto s0c, auto cntc, auto x0c, auto&& form) {
@@ -170,12 +166,12 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
         if constexpr (CNT > 0) {
           if (!ALL && (mm & (((1u << CNT) - 1) << s0)) == 0) return;
           const Operand<PREC> A = form();
-          if constexpr (PREC == kFP32 && !ALL) {   // a tile is 256 cycles of products: worth a branch
+          if constexpr (PREC == kFP32) {           // a tile is 256 cycles of products: worth a branch
             static_for<CNT>([&](auto c) {
               if ((mm >> (s0 + decltype(c)::value)) & 1) mma<PREC>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
             });
           } else {
-            static_for<PREC == kFP32 ? 8 : 3>([&](auto term) {
+            static_for<3>([&](auto term) {
               static_for<CNT>([&](auto c) {
                 mma_term<PREC, decltype(term)::value>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
               });
@@ -202,9 +198,10 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
       static_for<2>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         if (h == 1 && q == 1 && kF4 == 2) stage_store(cur ^ 1, kF4 - 1);
-        tiles(PS_C(kJLow + 3 * q), PS_C(2), PS_C(1), [&] { return product(plain(PS_C(0)), words(64 + uj[q])); });
+        if constexpr (NBLK > 1)
+          tiles(PS_C(kJLow + 3 * q), PS_C(2), PS_C(1), [&] { return product(Bop[0], words(64 + uj[q])); });
         if constexpr (NBLK > 3)
-          tiles(PS_C(kJHigh + 3 * q), PS_C(3), PS_C(0), [&] { return product(plain(PS_C(3)), words(128 + uj[q])); });
+          tiles(PS_C(kJHigh + 3 * q), PS_C(3), PS_C(0), [&] { return product(Bop[3], words(128 + uj[q])); });
       });
       if ((mm >> kJShared) != 0) {
         if (wave & 1) tiles(PS_C(kJShared), PS_C(2), PS_C(2), [&] { return product(words(xp), words(xj)); });
@@ -212,8 +209,10 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
       }
       corner(PS_C(kJDiag0 + 2), PS_C(2), diag0);
       corner(PS_C(kJDiag0 + 3), PS_C(3), diag0);
-      corner(PS_C(kJLow + 2), PS_C(3), [&] { return product(plain(PS_C(0)), words(64 + uj[0])); });
-      corner(PS_C(kJLow + 5), PS_C(3), [&] { return product(plain(PS_C(0)), words(64 + uj[1])); });
+      if constexpr (NBLK > 3) {
+        corner(PS_C(kJLow + 2), PS_C(3), [&] { return product(Bop[0], words(64 + uj[0])); });
+        corner(PS_C(kJLow + 5), PS_C(3), [&] { return product(Bop[0], words(64 + uj[1])); });
+      }
 #undef PS_C
     }
     __syncthreads();

@@ -36,7 +36,6 @@ hipError_t launch_half_spectrum_from_box(const cplx<float>* box, cplx<float>* hs
 // contract.hip
 struct CtrParams {
   const float* D;
-  const int* pair_uv;
   const int* slot_uni;     // [n_groups][waves][kSlots / 4]: one byte per slot
   const int* slot_lane;    // [n_groups][waves][16 rows][kSlots]: pair shells per lane
   const int* slot_tile;
@@ -45,7 +44,6 @@ struct CtrParams {
   long long G;
   int n_shells;
   int n_blk;
-  int n_pairs_padded;
   int n_tiles;
   int ksteps;
   int n_chunks;
@@ -69,7 +67,6 @@ constexpr int kRowStrideHost = 68;   // floats per staged float32 row
 constexpr int kMaxBlkHost = 4;       // the shell-block aligned order-3 kernel (<= 64 shells)
 constexpr int kMaxTileBlkHost = 8;   // the tile kernel, orders 2 to 4 (<= 128 shells)
 constexpr int kAdjPtsHost = 512;   // grid points per adjoint workgroup
-constexpr int kCntTuplesPerGroup = 1024;
 constexpr int kCntStageHost = 32;
 
 // Order 4 in split FP16, up to 64 shells (contract_pairs.hip): slots of `tiles` A blocks

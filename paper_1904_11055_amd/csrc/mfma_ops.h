@@ -95,13 +95,11 @@ __device__ __forceinline__ void mma(f32x4& acc, const Operand<PREC>& a, const Op
   }
 }
 
-// One of the matrix products of mma(): of the splits hi hi, hi lo, lo hi; of FP32 one of the
-// eight K-steps of 4.
+// One of the matrix products of mma() of a split: hi hi, hi lo, lo hi.
 template <int PREC, int TERM>
 __device__ __forceinline__ void mma_term(f32x4& acc, const Operand<PREC>& a, const Operand<PREC>& b) {
-  if constexpr (PREC == kFP32)
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[TERM], b.v[TERM], acc, 0, 0, 0);
-  else if constexpr (PREC == kBF16)
+  static_assert(PREC != kFP32, "the splits have three products");
+  if constexpr (PREC == kBF16)
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(TERM == 2 ? a.lo : a.hi, TERM == 1 ? b.lo : b.hi, acc, 0, 0, 0);
   else
     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(TERM == 2 ? a.lo : a.hi, TERM == 1 ? b.lo : b.hi, acc, 0, 0, 0);
@@ -227,12 +225,7 @@ __device__ __forceinline__ Operand<kFP16> form_pair_f16(const uint4 (*hi)[64], c
   return o;
 }
 
-// ORDER 2: A = shell block, B = shell block;  ORDER 3: A = pair block, B = shell
-// block;  ORDER 4: A = pair block, B = pair block;  ORDER 5: A = pair block, B =
-// triple block;  ORDER 6: A = triple block, B = triple block.
-//
-// A stage holds 64 grid points (two MFMA K-steps of 32).  16 waves share one stage;
-
+// The same from operands held in registers.
 __device__ __forceinline__ Operand<kFP16> pair_f16(const Operand<kFP16>& a, const Operand<kFP16>& b) {
   Operand<kFP16> o;
   o.hi = a.hi * b.hi;
@@ -251,7 +244,6 @@ __device__ __forceinline__ int tuple_unscale_exp(const unsigned* absmax, int b, 
   const int triples = prec != kFP16 ? 0 : order == 5 ? 1 : order == 6 ? 2 : 0;
   return triples * kTripleShift - ex;
 }
-
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
@@ -282,12 +274,5 @@ __device__ __forceinline__ void mma32_first(f32x16& acc, const Operand<PREC>& a,
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, b.hi, acc, 0, 0, 0);
   }
 }
-
-template <int PREC>
-__device__ __forceinline__ float operand_value(const Operand<PREC>& o, int r) {
-  if constexpr (PREC == kFP32) return o.v[r];
-  else return (float)o.hi[r] + (float)o.lo[r];
-}
-
 
 }  // namespace ps

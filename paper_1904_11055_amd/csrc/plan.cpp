@@ -104,7 +104,6 @@ struct polyspec_plan_s {
   // contraction tiling
   int n_pairs = 0, n_pairs_padded = 0, n_tiles = 0, n_groups = 0, ksteps = 0, n_chunks = 0;
   int red_groups = 0, red_cpg = 0;
-  int n_adj_active = 0;
   std::vector<int> pair_uv;
   // shell-block aligned order-3 schedule
   std::vector<int> wmask_host;     // adjoint: per v, bits 2 uc + mb of weight blocks
@@ -1184,7 +1183,6 @@ polyspec_status build_plan(polyspec_plan_s* p) {
           std::sort(t, t + 3);
           if (lookup[((size_t)t[0] * p->nb + t[1]) * p->nb + t[2]] >= 0) wmask[v] |= 1 << (2 * (u / 16) + m / 32);
         }
-    p->n_adj_active = p->nb;
     p->wmask_host = wmask;
     PS_TRY(upload(p, &p->wmask_d, wmask));
   }
@@ -1477,7 +1475,6 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
   } else {
     ps::CtrParams cp;
     cp.D = p->D;
-    cp.pair_uv = (const int*)p->pairs_d.p;
     const auto& rows = p->row_groups[p->order == 6 && p->prec == POLYSPEC_FP32];
     const bool hi = p->order >= 5;
     cp.slot_uni = (const int*)(hi ? rows.slots : p->slots_d).p;
@@ -1488,7 +1485,6 @@ static polyspec_status contract_launch(polyspec_plan_t p, bool accumulate, long 
     cp.G = launch_points(p);
     cp.n_shells = p->nb;
     cp.n_blk = p->n_blk;
-    cp.n_pairs_padded = p->n_pairs_padded;
     cp.n_tiles = p->n_tiles;
     cp.ksteps = p->ksteps;
     cp.n_chunks = p->n_chunks;
