@@ -50,8 +50,9 @@ def kernel_source_hash() -> str:
     """Hash of the sources of the matrix-core kernels (the contraction and the adjoint)."""
     h = hashlib.sha256()
     for f in ("contract_tiles.h", "contract_tiles_lo.hip", "contract_tiles_hi.hip", "contract_j3.hip",
-              "contract_pairs.hip", "adjoint.h", "adjoint.hip", "adjoint_fp16.hip", "adjoint4_fp16.hip", "adjoint_sym.h", "adjoint_sym_fp32.hip",
-              "adjoint_sym_bf16.hip", "adjoint4_sym_fp32.hip", "adjoint4_sym_bf16.hip",
+              "contract_pairs.hip", "adjoint.h", "adjoint.hip", "adjoint_fp16.hip", "adjoint4_fp16.hip",
+              "adjoint_sym.h", "adjoint_sym_fp32.hip", "adjoint_sym_bf16.hip", "adjoint4_sym_fp32.hip",
+              "adjoint4_sym_bf16.hip",
               "mfma_ops.h", "fft_core.h", "common.h", "kernels.h"):
         with open(os.path.join(ROOT, "paper_1904_11055_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
@@ -272,7 +273,8 @@ def main():
                         load_traffic(ctr_kernel, args.workload, args.precision))
     if has_backward:
         n_w = adjoint_weight_entries(plan.tuples)
-        adj_kernel = ("adjoint" if order == 3 else "adjoint4") + ("_gemm" if bwd_name == "fp16" and not streamed else "_sym")
+        adj_kernel = (("adjoint" if order == 3 else "adjoint4") +
+                      ("_gemm" if bwd_name == "fp16" and not streamed else "_sym"))
         plan.precision = bwd_code         # the issued products of the adjoint's own precision
         adj_issued = ps.polyspec_issued_flops(plan.handle, "adj_gemm")
         plan.precision = prec

@@ -285,7 +285,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_gemm(const float* __re
   };
   auto w_store = [&](int buf, int q) {
 #pragma unroll
-    for (int k = 0; k < kAdjPiece; ++k) *reinterpret_cast<u32x4*>(&wst[buf][(q * kAdjPiece + k) * kAdjThreads + tid]) = wp[k];
+    for (int k = 0; k < kAdjPiece; ++k)
+      *reinterpret_cast<u32x4*>(&wst[buf][(q * kAdjPiece + k) * kAdjThreads + tid]) = wp[k];
   };
   for (int q = 0; q < kAdjVG; ++q) {
     w_load(0, q);

@@ -5,20 +5,18 @@
 
 namespace ps {
 
-extern template hipError_t launch_adjoint_sym_prec<kFP32>(const float*, const uint4*, const float2*, int, int, long long, float*,
-                                                          cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
-extern template hipError_t launch_adjoint_sym_prec<kBF16>(const float*, const uint4*, const float2*, int, int, long long, float*,
-                                                          cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
-extern template hipError_t launch_adjoint4_sym_prec<kFP32>(const float*, const uint4*, const float2*, const int*, int, long long,
-                                                           float*, cplx<float>*, const cplx<float>*, Geom, int,
-                                                           hipStream_t);
-extern template hipError_t launch_adjoint4_sym_prec<kBF16>(const float*, const uint4*, const float2*, const int*, int, long long,
-                                                           float*, cplx<float>*, const cplx<float>*, Geom, int,
-                                                           hipStream_t);
+#define PS_SYM_ARGS const float*, const uint4*, const float2*
+#define PS_OUT_ARGS long long, float*, cplx<float>*, const cplx<float>*, Geom, int, hipStream_t
+extern template hipError_t launch_adjoint_sym_prec<kFP32>(PS_SYM_ARGS, int, int, PS_OUT_ARGS);
+extern template hipError_t launch_adjoint_sym_prec<kBF16>(PS_SYM_ARGS, int, int, PS_OUT_ARGS);
+extern template hipError_t launch_adjoint4_sym_prec<kFP32>(PS_SYM_ARGS, const int*, int, PS_OUT_ARGS);
+extern template hipError_t launch_adjoint4_sym_prec<kBF16>(PS_SYM_ARGS, const int*, int, PS_OUT_ARGS);
 hipError_t launch_adjoint4_gemm_fp16(const float*, const uint4*, const int*, const unsigned*, const unsigned long long*,
-                                     int, long long, float*, cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
-hipError_t launch_adjoint_gemm_fp16(const float*, const uint4*, const int*, const unsigned*, const unsigned long long*, int,
-                                    long long, float*, cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
+                                     int, PS_OUT_ARGS);
+hipError_t launch_adjoint_gemm_fp16(const float*, const uint4*, const int*, const unsigned*, const unsigned long long*,
+                                    int, PS_OUT_ARGS);
+#undef PS_OUT_ARGS
+#undef PS_SYM_ARGS
 
 // dL/dB_t f / (N^3 n_t) times the number of times m occurs in t = sort(shells), or 0
 // when t does not close.
@@ -50,7 +48,8 @@ __device__ __forceinline__ double adj_weight(const double* __restrict__ grad, co
 // row's scale e_m, the inverse of the rest's field scales, and for order 4 the 2^7
 // that brings the triple products into range.
 template <int ORDER>
-__device__ __forceinline__ int adj_weight_exp(const unsigned* absmax, int b, int n_shells, const int (&rest)[ORDER - 1]) {
+__device__ __forceinline__ int adj_weight_exp(const unsigned* absmax, int b, int n_shells,
+                                              const int (&rest)[ORDER - 1]) {
   int ex = ORDER == 4 ? kTripleShift : 0;
 #pragma unroll
   for (int j = 0; j < ORDER - 1; ++j) ex -= shell_scale_exp(absmax, b * n_shells + rest[j]);
@@ -176,8 +175,8 @@ __global__ void adjoint_sym_weights(const double* __restrict__ grad, const doubl
   int k, m, uc;
   sym_lane(kb, idx, ln, k, m, uc);
   k += 2 * pair;
-  uint4* base = W + (((size_t)b * sym_base((n_shells + 15) / 16) + sym_base(kb)) + (size_t)(pair % 8) * sym_blocks(kb) + idx) *
-                        kSymBlockWords;
+  uint4* base = W + (size_t)b * sym_words(n_shells) +
+                (sym_base(kb) + (size_t)(pair % 8) * sym_blocks(kb) + idx) * kSymBlockWords;
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const int u = 16 * uc + 8 * (ln >> 5) + r;
@@ -313,8 +312,8 @@ hipError_t launch_adjoint_gemm(int prec, const float* D, const uint4* W, const i
 }
 
 hipError_t launch_adjoint4_gemm(int prec, const float* D, const uint4* W, const int* imask, const int* pmask,
-                                const unsigned* absmax, const unsigned long long* rowmax, int n_shells, long long G, float* A,
-                                cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st) {
+                                const unsigned* absmax, const unsigned long long* rowmax, int n_shells, long long G,
+                                float* A, cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st) {
   const bool fused = adjoint_fuses_rows(g.N);
   if (fused == (H2 == nullptr) || fused == (A != nullptr) || n_shells > kAdj4MaxShells || G % kAdjPts != 0)
     return hipErrorInvalidValue;

@@ -3,7 +3,8 @@
 
 namespace ps {
 
-template hipError_t launch_adjoint4_sym_prec<kFP32>(const float*, const uint4*, const float2*, const int*, int, long long, float*,
-                                                    cplx<float>*, const cplx<float>*, Geom, int, hipStream_t);
+template hipError_t launch_adjoint4_sym_prec<kFP32>(const float*, const uint4*, const float2*, const int*, int,
+                                                    long long, float*, cplx<float>*, const cplx<float>*, Geom, int,
+                                                    hipStream_t);
 
 }  // namespace ps

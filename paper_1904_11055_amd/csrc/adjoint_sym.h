@@ -7,7 +7,7 @@
 // Each triplet is multiplied twice, by its two smaller sides, instead of three times
 // by every side as in a_m = sum_{u <= v} W[m][(u, v)] d_u d_v, and the matrices are the
 // (k, k) corner instead of every m.  For an alias-free plan the triangle bound
-// k <= i + j + 2 (0-based) empties another corner: 64 shells take 210 32 x 32 x 16
+// k <= i + j + 2 (0-based) empties another corner: 64 shells take 211 32 x 32 x 16
 // products per 32 points where the other form takes 304.
 //
 // Matrix products.  Y_k is computed in 32-row chains over the 16-shell chunks uc of u:
@@ -131,8 +131,9 @@ __device__ __forceinline__ void sym_add(float (&acc)[kAdjPB][KB][8], float (&q)[
 // transform's paired stores: 75.4 with 8 waves).
 template <int PREC, int NF, int KB>
 __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __restrict__ D, const uint4* __restrict__ W,
-                                                            const float2* __restrict__ equal, int n_shells, int dense, long long G,
-                                                            float* __restrict__ A, cplx<float>* __restrict__ H2,
+                                                            const float2* __restrict__ equal, int n_shells,
+                                                            int dense, long long G, float* __restrict__ A,
+                                                            cplx<float>* __restrict__ H2,
                                                             const cplx<float>* __restrict__ tw, Geom g) {
   static_assert(PREC != kFP16, "the FP16 split scales every weight row by its own power of two: adjoint_gemm");
   __shared__ __attribute__((aligned(16))) unsigned char lds[sym_lds_bytes<NF, KB>()];
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
   const int b = blockIdx.y;
   const long long xw = (long long)blockIdx.x * kAdjPts + wave * 32 * kAdjPB + col;
   const float* Db = D + (size_t)b * n_shells * G;
-  const uint4* Wb = W + (size_t)b * sym_base((n_shells + 15) / 16) * kSymBlockWords;
+  const uint4* Wb = W + (size_t)b * sym_words(n_shells);
 
   AdjFields<PREC, KB> f;
   adj_load_fields<PREC, KB>(f, Db, G, xw, hh, n_shells, nullptr, b);
@@ -445,11 +446,12 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
 }
 
 template <int PREC>
-hipError_t launch_adjoint_sym_prec(const float* D, const uint4* W, const float2* equal, int n_shells, int dense, long long G, float* A,
-                                   cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st) {
+hipError_t launch_adjoint_sym_prec(const float* D, const uint4* W, const float2* equal, int n_shells, int dense,
+                                   long long G, float* A, cplx<float>* H2, const cplx<float>* tw, Geom g, int batch,
+                                   hipStream_t st) {
   dim3 grid((unsigned)(G / kAdjPts), batch);
-#define L2(NF, KB) hipLaunchKernelGGL((adjoint_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, equal, n_shells, \
-                                      dense, G, A, H2, tw, g)
+#define L2(NF, KB) hipLaunchKernelGGL((adjoint_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, equal, \
+                                      n_shells, dense, G, A, H2, tw, g)
 #define L(NF)                          \
   do {                                 \
     if (n_shells <= 16) L2(NF, 1);     \
@@ -471,12 +473,12 @@ hipError_t launch_adjoint_sym_prec(const float* D, const uint4* W, const float2*
 }
 
 template <int PREC>
-hipError_t launch_adjoint4_sym_prec(const float* D, const uint4* W, const float2* equal, const int* pmask, int n_shells, long long G,
-                                    float* A, cplx<float>* H2, const cplx<float>* tw, Geom g, int batch,
-                                    hipStream_t st) {
+hipError_t launch_adjoint4_sym_prec(const float* D, const uint4* W, const float2* equal, const int* pmask,
+                                    int n_shells, long long G, float* A, cplx<float>* H2, const cplx<float>* tw,
+                                    Geom g, int batch, hipStream_t st) {
   dim3 grid((unsigned)(G / kAdjPts), batch);
-#define L2(NF, KB) hipLaunchKernelGGL((adjoint4_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, equal, pmask, \
-                                      n_shells, G, A, H2, tw, g)
+#define L2(NF, KB) hipLaunchKernelGGL((adjoint4_sym<PREC, NF, KB>), grid, dim3(kAdjThreads), 0, st, D, W, equal, \
+                                      pmask, n_shells, G, A, H2, tw, g)
 #define L(NF)                           \
   do {                                  \
     if (n_shells <= 16) L2(NF, 1);      \

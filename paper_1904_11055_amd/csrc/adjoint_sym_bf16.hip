@@ -3,7 +3,8 @@
 
 namespace ps {
 
-template hipError_t launch_adjoint_sym_prec<kBF16>(const float*, const uint4*, const float2*, int, int, long long, float*, cplx<float>*,
-                                                   const cplx<float>*, Geom, int, hipStream_t);
+template hipError_t launch_adjoint_sym_prec<kBF16>(const float*, const uint4*, const float2*, int, int,
+                                                   long long, float*, cplx<float>*, const cplx<float>*, Geom, int,
+                                                   hipStream_t);
 
 }  // namespace ps

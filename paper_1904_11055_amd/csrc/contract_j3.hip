@@ -16,7 +16,7 @@ namespace ps {
 // the second kind mirrored, 15 - a and 1 + a), a = 0..6 for wave a, and the full j = 15
 // (j = 0) for wave 7.  The half-full j = 7 (j = 8) of two blocks share a ninth operand,
 // whose four columns blocks go to waves 0 to 3, two each.  64 unit shells take 186 tiles
-// instead of 260 with one operand per j, and 66 operands formed per step instead of 96
+// instead of 260 with one operand per j, and 66 different operands per step instead of 96
 // (512^3: 47.5 ms before).  Both rows of a product come from LDS words at lane-dependent
 // slots, the rest of a 32-point step from registers.  A per-wave mask says which tiles
 // hold a candidate tuple.
@@ -60,14 +60,18 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
   const int b = blockIdx.z;
 
   for (int i = tid; i < kMaxBlk * 16; i += kJThreads)
-    lds_scale[i] = PREC != kFP16 ? 1.f : i < p.n_shells ? ldexpf(1.0f, shell_scale_exp(p.absmax, b * p.n_shells + i)) : 0.f;
+    lds_scale[i] = PREC != kFP16     ? 1.f
+                   : i < p.n_shells ? ldexpf(1.0f, shell_scale_exp(p.absmax, b * p.n_shells + i))
+                                    : 0.f;
   for (int i = tid; i < 4 * kMaxBlk * 64; i += kJThreads) {
     const int bh = i / (kMaxBlk * 64), kb = (i / 64) % kMaxBlk, ln = i % 64;
     if (kb * 16 + (ln & 15) >= p.n_shells) {
       opHi[bh >> 1][bh & 1][kb][op_slot(ln)] = make_uint4(0, 0, 0, 0);
       opLo[bh >> 1][bh & 1][kb][op_slot(ln)] = make_uint4(0, 0, 0, 0);
-      if constexpr (PREC == kBF16)
-        spHi[bh >> 1][bh & 1][kb * 64 + op_slot(ln)] = spLo[bh >> 1][bh & 1][kb * 64 + op_slot(ln)] = make_uint4(0, 0, 0, 0);
+      if constexpr (PREC == kBF16) {
+        spHi[bh >> 1][bh & 1][kb * 64 + op_slot(ln)] = make_uint4(0, 0, 0, 0);
+        spLo[bh >> 1][bh & 1][kb * 64 + op_slot(ln)] = make_uint4(0, 0, 0, 0);
+      }
     }
   }
   __syncthreads();
@@ -168,7 +172,8 @@ __global__ __launch_bounds__(kJThreads, 1) void contract_j3(CtrJParams p) {
           const Operand<PREC> A = form();
           if constexpr (PREC == kFP32) {           // a tile is 256 cycles of products: worth a branch
             static_for<CNT>([&](auto c) {
-              if ((mm >> (s0 + decltype(c)::value)) & 1) mma<PREC>(acc[s0 + decltype(c)::value], A, Bop[x0 + decltype(c)::value]);
+              constexpr int s = s0 + decltype(c)::value;
+              if ((mm >> s) & 1) mma<PREC>(acc[s], A, Bop[x0 + decltype(c)::value]);
             });
           } else {
             static_for<3>([&](auto term) {

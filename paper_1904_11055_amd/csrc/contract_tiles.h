@@ -94,7 +94,8 @@ __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
 #pragma unroll
   for (int q = 0; q < SP; ++q) {
     pre[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (st_row[q] < p.n_shells) pre[q] = *reinterpret_cast<const float4*>(Db + (size_t)st_row[q] * p.G + x_base + st_col[q]);
+    if (st_row[q] < p.n_shells)
+      pre[q] = *reinterpret_cast<const float4*>(Db + (size_t)st_row[q] * p.G + x_base + st_col[q]);
   }
   __syncthreads();
 #pragma unroll
@@ -123,7 +124,8 @@ __global__ __launch_bounds__(kCtrThreads, 1) void contract_tiles(CtrParams p) {
 #pragma unroll
       for (int q = 0; q < SP; ++q)
         if (st_row[q] < p.n_shells)
-          pre[q] = *reinterpret_cast<const float4*>(Db + (size_t)st_row[q] * p.G + x_base + (ks + 1) * kKStep + st_col[q]);
+          pre[q] = *reinterpret_cast<const float4*>(Db + (size_t)st_row[q] * p.G + x_base + (ks + 1) * kKStep +
+                                                    st_col[q]);
     }
     const float* S = stage[cur];
 #pragma unroll

@@ -8,8 +8,9 @@
 // 11 A blocks per group), one forming while the other multiplies.  256^3, against a
 // formation per tile: order 5 with 16 shells (95 tiles over 9 A and 51 B blocks) FP16 8.35 ->
 // 4.75 ms, BF16 6.49 -> 4.08, FP32 8.48 -> 7.12; order 6 with 8 shells (19 tiles over 8 and 8)
-// FP16 3.44 -> 1.54, FP32 4.14 -> 2.41.  What is left at order 5 is mostly LDS: about 7000
-// of 9600 cycles per stage for the row reads of 102 B blocks and the A operands.
+// FP16 3.44 -> 1.54, FP32 4.14 -> 1.80 (units of three tiles).  What is left at order 5 is mostly LDS:
+// the row reads of 102 B blocks and the A operands keep it active in 5900 of 10600 cycles per
+// stage, 1300 of them bank conflicts, where the matrix cores are busy in 2300 (FP16, counters).
 #include "mfma_ops.h"
 
 namespace ps {
@@ -54,8 +55,8 @@ __global__ __launch_bounds__(kHiThreads, 4) void contract_rows(CtrParams p) {
   const int st_row = tid >> 4;
   const bool st_on = st_row < p.n_shells;
   const float st_scale = st_on ? ldexpf(1.0f, shell_scale_exp(p.absmax, b * p.n_shells + st_row)) : 0.f;
-  const float* src = p.D + ((size_t)b * p.n_shells + (st_on ? st_row : 0)) * p.G + (long long)chunk * p.ksteps * kKStep +
-                     (tid & 15) * 4;
+  const float* src = p.D + ((size_t)b * p.n_shells + (st_on ? st_row : 0)) * p.G +
+                     (long long)chunk * p.ksteps * kKStep + (tid & 15) * 4;
   char* dst = stage + st_row * kRowB + (tid & 15) * 16;
   auto store = [&](int buf, float4 v) {
     if (st_on)
@@ -79,7 +80,8 @@ __global__ __launch_bounds__(kHiThreads, 4) void contract_rows(CtrParams p) {
   const size_t gw = (size_t)group * kHiWaves + wave;
   int un[(kHiSlots + 3) / 4], bw[kHiSlots];
 #pragma unroll
-  for (int i = 0; i < (kHiSlots + 3) / 4; ++i) un[i] = __builtin_amdgcn_readfirstlane(p.slot_uni[gw * (kSlotsMax / 4) + i]);
+  for (int i = 0; i < (kHiSlots + 3) / 4; ++i)
+    un[i] = __builtin_amdgcn_readfirstlane(p.slot_uni[gw * (kSlotsMax / 4) + i]);
 #pragma unroll
   for (int s = 0; s < kHiSlots; ++s) bw[s] = p.slot_lane[(gw * 16 + row) * kSlotsMax + s];
   f32x4 acc[kHiSlots];

@@ -35,7 +35,12 @@ hipError_t launch_contract(int prec, int order, const CtrParams& p, int n_groups
   // workgroups per CU; 8 blocks take up to 128 shells
 #define L(P, O, MB) hipLaunchKernelGGL((contract_tiles<P, O, MB>), grid, dim3(kCtrThreads), 0, st, p)
 #define BY_MB(P, O) do { if (p.n_blk <= 4) L(P, O, 4); else L(P, O, 8); } while (0)
-#define BY_PREC(O) do { if (prec == kFP32) BY_MB(kFP32, O); else if (prec == kBF16) BY_MB(kBF16, O); else BY_MB(kFP16, O); } while (0)
+#define BY_PREC(O)                             \
+  do {                                         \
+    if (prec == kFP32) BY_MB(kFP32, O);        \
+    else if (prec == kBF16) BY_MB(kBF16, O);   \
+    else BY_MB(kFP16, O);                      \
+  } while (0)
   if (order == 2) BY_PREC(2);
   else if (order == 3) {
     // FP16 with up to 64 shells: contract_j3

@@ -45,8 +45,9 @@ struct FftCfg<double> {
 // enough that 256 threads have a radix-8 butterfly each.  Against elems / N pencils
 // everywhere: shell pass 2 at 128^3 x 192 fields of 25 columns 0.50 -> 0.23 ms, 256^3 / 40
 // shells 0.86 -> 0.67, 64^3 / 16 shells 22 -> 10 us; the adjoint's q2 at 128^3 x 192 fields
-// 0.31 -> 0.23.  The inverse passes' values do not depend on the choice (fft_stage); the
-// forward ones' last bits do, so the input's transform, 2 us of a 64^3 spectrum, keeps elems / N.
+// 0.31 -> 0.23.  The compiler rounds narrower blocks differently in the last bit.  The inverse passes
+// keep the values of elems / N pencils all the same (fft_stage); of the forward ones only the
+// gradient's are narrowed, and the input's transform, 2 us of a 64^3 spectrum, keeps elems / N.
 template <typename T>
 constexpr int col_pencils(int N, int elems) {
   if (sizeof(T) == 8) return elems / N;
@@ -646,7 +647,8 @@ hipError_t launch_r2c_q2(const cplx<float>* H2, cplx<float>* H1, const cplx<floa
   const int reps = loop_reps(g.S1, cb * nz);
   dim3 grid(cb, g.S1 / reps, nz);
   switch (g.N) {
-#define CASE(n) case n: hipLaunchKernelGGL((r2c_q2<n, GRAD>), grid, dim3(kFftThreads), 0, st, H2, H1, tw, g, reps); break;
+#define CASE(n) \
+    case n: hipLaunchKernelGGL((r2c_q2<n, GRAD>), grid, dim3(kFftThreads), 0, st, H2, H1, tw, g, reps); break;
     PS_FOR_EACH_N(CASE)
 #undef CASE
     default: return hipErrorInvalidValue;

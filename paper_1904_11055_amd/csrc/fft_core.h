@@ -115,10 +115,13 @@ __device__ __forceinline__ void build_stage_twiddles(cplx<T>* stw, const cplx<T>
 // After the stage every run of p*R consecutive outputs is a finished sub-DFT.
 // tws: this stage's twiddle table, entry (r - 1) * p + k = exp(2 pi i k r / (p R)).
 //
-// PO, pen0: the pencils are pen0 .. pen0 + P - 1 of PO, and the values are bit for bit those of
-// a block that holds all PO.  There the compiler rounds, of the two products in one element times
-// an eighth root, one in the last NT butterflies of the second stage and the other in the rest;
-// where P differs from PO that choice is written out.  (Inverse transforms only.)
+// PO, pen0: the pencils are pen0 .. pen0 + P - 1 of PO, and the values are those of a block that
+// holds all PO, so that fields and spectra keep their last bits.  Of the two products in one
+// element times an eighth root, the compiler rounds one in the last NT butterflies of such a
+// block's second stage and fuses it in the rest; where P differs from PO that choice is written
+// out.  Either is as accurate.  This follows the code of one compiler (hipcc of ROCm 7.2), in which the
+// fields of N = 32 to 256 were compared bit for bit; another may differ by 1 ulp of a field.
+// (Inverse transforms only.)
 template <typename T, int N, int P, int NS, int R, int S, int NT = kFftThreads, int PO = P>
 __device__ __forceinline__ void fft_stage(cplx<T>* buf, int p, const cplx<T>* tws, int pen0 = 0) {
   constexpr int NB = N / R;

@@ -112,7 +112,8 @@ struct JGroup { int slot, count, block, plan_blk; };
 constexpr JGroup kJGroups[] = {{kJDiag0, 2, 0, 1}, {kJDiag1, 3, 1, 2}, {kJDiag2, 3, 0, 3}, {kJDiag3, 4, 0, 4},
                                {kJLow, 2, 1, 2},   {kJLow + 3, 2, 1, 2}, {kJHigh, 3, 0, 4}, {kJHigh + 3, 3, 0, 4}};
 // Slots multiplied alone, for the shell blocks 2 and 3 of the small shells' operands.
-constexpr JGroup kJCorners[] = {{kJDiag0 + 2, 1, 2, 3}, {kJDiag0 + 3, 1, 3, 4}, {kJLow + 2, 1, 3, 4}, {kJLow + 5, 1, 3, 4}};
+constexpr JGroup kJCorners[] = {{kJDiag0 + 2, 1, 2, 3}, {kJDiag0 + 3, 1, 3, 4}, {kJLow + 2, 1, 3, 4},
+                                {kJLow + 5, 1, 3, 4}};
 struct JPlace {
   int wave, slot, row, col;
 };
@@ -162,8 +163,8 @@ hipError_t launch_counts_wedge(int order, const double* cw, long long nwedge, co
 hipError_t launch_reduce_dd(const double2* part, double2* tmp, int n_chunks, int cpg, int n_groups, long long n_ent,
                             hipStream_t st);
 // Adjoint products (adjoint.h).  FP16 (prec 2) scales every weight row m by its own
-// power of two, found from rowmax[b][64] (float64 bits, written by the weights launch; FP32 and BF16 keep the weights of sym_equal there);
-// absmax holds the per-shell field maxima of the forward's FP16 scaling.
+// power of two, found from rowmax[b][64] (float64 bits, written by the weights launch; FP32 and
+// BF16 keep the weights of sym_equal there); absmax holds the per-shell field maxima of the forward's FP16 scaling.
 hipError_t launch_adjoint_weights(const double* grad, const double* fnorm, const int* lookup, int n_shells,
                                   int n_closing, int prec, const unsigned* absmax, unsigned long long* rowmax,
                                   uint4* W, int batch, hipStream_t st);
@@ -174,8 +175,8 @@ hipError_t launch_adjoint_gemm(int prec, const float* D, const uint4* W, const i
                                const unsigned long long* rowmax, int n_shells, bool dense, long long G, float* A,
                                cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st);
 // Order 3 in FP32 and BF16, the symmetric form (adjoint_sym.h): partners k in pairs, 32-row
-// chains over the 16-shell chunks of u.  Weight blocks (32 rows x 16 u) of one pair of partners in shell block kb, and pairs
-// staged together (at most 18 blocks of 2 KB per stage).
+// chains over the 16-shell chunks of u.  Weight blocks (32 rows x 16 u) of one pair of partners in
+// shell block kb, and pairs staged together (at most 18 blocks of 2 KB per stage).
 __host__ __device__ constexpr int sym_blocks(int kb) { return (kb + 1) * (kb + 1); }
 __host__ __device__ constexpr int sym_stage_pairs(int kb) { return 8 >> kb; }
 __host__ __device__ constexpr int sym_p_chains(int kb) { return kb == 0 ? 1 : kb == 1 ? 0 : kb - 1; }
@@ -188,8 +189,12 @@ __host__ __device__ constexpr int sym_base(int kb) {
 
 constexpr int kSymBlockWords = 2 * 64;   // 16-byte words of a block: hi and lo of its 64 lanes
 constexpr int kSymCopyWords = 512;       // one word per thread: a stage is copied in whole rounds
-__host__ __device__ constexpr int sym_stage_words(int kb) { return sym_stage_pairs(kb) * sym_blocks(kb) * kSymBlockWords; }
-__host__ __device__ constexpr int sym_rounds(int kb) { return (sym_stage_words(kb) + kSymCopyWords - 1) / kSymCopyWords; }
+__host__ __device__ constexpr int sym_stage_words(int kb) {
+  return sym_stage_pairs(kb) * sym_blocks(kb) * kSymBlockWords;
+}
+__host__ __device__ constexpr int sym_rounds(int kb) {
+  return (sym_stage_words(kb) + kSymCopyWords - 1) / kSymCopyWords;
+}
 // Weight words of one batch entry of order 3, and of what the last round of a stage reads past
 // its end (the stages of block 2, 18 blocks of 128 words in five rounds).
 __host__ __device__ constexpr int sym_words(int n_shells) { return sym_base((n_shells + 15) / 16) * kSymBlockWords; }
@@ -249,8 +254,8 @@ hipError_t launch_adjoint4_weights(const double* grad, const double* fnorm, cons
                                    int n_closing, int prec, const unsigned* absmax, unsigned long long* rowmax,
                                    uint4* W, int batch, hipStream_t st);
 hipError_t launch_adjoint4_gemm(int prec, const float* D, const uint4* W, const int* imask, const int* pmask,
-                                const unsigned* absmax, const unsigned long long* rowmax, int n_shells, long long G, float* A,
-                                cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st);
+                                const unsigned* absmax, const unsigned long long* rowmax, int n_shells, long long G,
+                                float* A, cplx<float>* H2, const cplx<float>* tw, Geom g, int batch, hipStream_t st);
 
 // util.hip
 constexpr size_t kStaticScratchBytes = (size_t)128 << 20;   // polyspec_forward_static's workspace

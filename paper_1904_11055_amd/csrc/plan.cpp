@@ -278,7 +278,8 @@ void set_chunking(polyspec_plan_s* p) {
   while (steps % ks) --ks;
   p->ksteps = (int)ks;
   p->n_chunks = (int)(steps / ks);
-  // the shell-block aligned kernel works on whole 256-point stages
+  // the shell-block aligned kernel takes four stages or more to a chunk (N = 32: 128 chunks to
+  // reduce instead of 512)
   long long ksj = std::max(4LL, ks);
   while (steps % ksj) ++ksj;
   p->ksteps_j = (int)ksj;
@@ -608,7 +609,8 @@ polyspec_status pack_order4(polyspec_plan_s* p, const std::vector<TileKey>& tlis
       std::vector<std::vector<Slot>> g = cut(ka, kb);
       double cost = 0;   // see above
       for (const auto& x : g)
-        cost += 1000.0 + 80.0 * (double)blocks_of(x).size() + 48.0 * T / 4.0 * (double)(((int)x.size() + W - 1) / W * W);
+        cost += 1000.0 + 80.0 * (double)blocks_of(x).size() +
+                48.0 * T / 4.0 * (double)(((int)x.size() + W - 1) / W * W);
       if (best < 0 || cost < best) { best = cost; groups = std::move(g); }
     }
   std::vector<int> sa, sb, tile, grp, ngrp;
@@ -636,9 +638,9 @@ polyspec_status pack_order4(polyspec_plan_s* p, const std::vector<TileKey>& tlis
           tile[at * T + a] = sl.second[a];
         }
         // a slot of two is multiplied as a whole, one of four by halves
-        p->n_issued4 += T == 2 ? 2 : 2 * ((sl.second[0] >= 0 || sl.second[1] >= 0) + (sl.second[2] >= 0 || sl.second[3] >= 0));
-        sb[at] = local(sl.first.second) | (load ? 0x100 : 0) | (sl.second[0] >= 0 || sl.second[1] >= 0 ? 0x200 : 0) |
-                 (sl.second[2] >= 0 || sl.second[3] >= 0 ? 0x400 : 0);
+        const bool lo = sl.second[0] >= 0 || sl.second[1] >= 0, hi = sl.second[2] >= 0 || sl.second[3] >= 0;
+        p->n_issued4 += T == 2 ? 2 : 2 * (lo + hi);
+        sb[at] = local(sl.first.second) | (load ? 0x100 : 0) | (lo ? 0x200 : 0) | (hi ? 0x400 : 0);
       }
     }
     ngrp.push_back((int)blocks.size());
@@ -1224,10 +1226,11 @@ void release(polyspec_plan_s* p) {
   p->ev_pending.clear();
   for (hipEvent_t e : p->ev_pool) (void)hipEventDestroy(e);
   p->ev_pool.clear();
-  DevBuf* bufs[] = {&p->tw32, &p->shell_q, &p->qmax_d, &p->pairs_d, &p->slots_d, &p->slot_lane_d, &p->slot_tile_d,   &p->ent_d,
-                    &p->bins_d, &p->fnorm_d, &p->lookup_d, &p->wmask_d, &p->pmask_d, &p->flag_d, &p->jtile_d, &p->jmask_d,
-                    &p->ent_j_d, &p->closing_of_ent_d, &p->closing_of_ent_j_d, &p->a_rows_d, &p->sa4_d, &p->sb4_d, &p->tile4_d, &p->grp4_d, &p->ngrp4_d,
-                    &p->own_ws};
+  DevBuf* bufs[] = {&p->tw32,     &p->shell_q,  &p->qmax_d,  &p->pairs_d, &p->slots_d,          &p->slot_lane_d,
+                    &p->slot_tile_d, &p->ent_d, &p->bins_d,  &p->fnorm_d, &p->lookup_d,         &p->wmask_d,
+                    &p->pmask_d,  &p->flag_d,   &p->jtile_d, &p->jmask_d, &p->ent_j_d,          &p->closing_of_ent_d,
+                    &p->closing_of_ent_j_d,     &p->a_rows_d, &p->sa4_d,  &p->sb4_d,            &p->tile4_d,
+                    &p->grp4_d,   &p->ngrp4_d,  &p->own_ws};
   for (DevBuf* b : bufs) dev_free(b);
   for (auto& r : p->row_groups)
     for (DevBuf* b : {&r.slots, &r.slot_lane, &r.slot_tile, &r.grp_blk, &r.grp_nblk}) dev_free(b);
@@ -1306,7 +1309,8 @@ polyspec_status polyspec_workspace_size(polyspec_plan_t p, size_t* bytes) {
 polyspec_status polyspec_set_workspace(polyspec_plan_t p, void* d_ptr, size_t bytes) {
   if (!p) return POLYSPEC_ERR_INVALID_ARG;
   if (p->ws) return p->fail(POLYSPEC_ERR_STATE, "workspace already set or allocated");
-  if (!d_ptr || ((uintptr_t)d_ptr & 255)) return p->fail(POLYSPEC_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
+  if (!d_ptr || ((uintptr_t)d_ptr & 255))
+    return p->fail(POLYSPEC_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
   if (bytes < layout_of(p).total) return p->fail(POLYSPEC_ERR_INVALID_ARG, "workspace too small");
   p->ws = (char*)d_ptr;
   p->ws_size = bytes;
@@ -1356,8 +1360,8 @@ static polyspec_status shell_slab(polyspec_plan_t p, int slab, unsigned* absmax_
   }
   const int nz = p->batch * p->nb;
   hipStream_t st = p->stream;
-  PS_TIMED(p, POLYSPEC_PH_SHELL_P2, ps::launch_c2r_p2<float>(p->H1, (const int*)p->qmax_d.p, p->H2, (const cplx<float>*)p->tw32.p, gs, nz,
-                                     st));
+  PS_TIMED(p, POLYSPEC_PH_SHELL_P2, ps::launch_c2r_p2<float>(p->H1, (const int*)p->qmax_d.p, p->H2,
+                                                             (const cplx<float>*)p->tw32.p, gs, nz, st));
   PS_TIMED(p, POLYSPEC_PH_SHELL_P3, ps::launch_c2r_p3(p->H2, (const int*)p->qmax_d.p, p->D, absmax_part,
                                                       (const cplx<float>*)p->tw32.p, gs, nz, st));
   return POLYSPEC_OK;
@@ -1383,14 +1387,17 @@ static polyspec_status shells_impl(polyspec_plan_t p, const void* d_delta) {
     PS_HIP(p, ps::launch_box_from_half_spectrum((const cplx<float>*)d_delta, p->box, gin, p->batch, st));
   } else {
     // the input transform uses H2 and H1 as scratch (sized for it in streamed plans too)
-    PS_TIMED(p, POLYSPEC_PH_INPUT_Q3, ps::launch_r2c_q3((const float*)d_delta, p->H2, (const cplx<float>*)p->tw32.p, gin, p->batch, st));
-    PS_TIMED(p, POLYSPEC_PH_INPUT_Q2, ps::launch_r2c_q2<false>(p->H2, p->H1, (const cplx<float>*)p->tw32.p, gin, p->batch, st));
-    PS_TIMED(p, POLYSPEC_PH_INPUT_Q1, ps::launch_r2c_q1<false>(p->H1, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, p->box,
-                                       (const cplx<float>*)p->tw32.p, gin, p->batch, st));
+    const cplx<float>* tw = (const cplx<float>*)p->tw32.p;
+    PS_TIMED(p, POLYSPEC_PH_INPUT_Q3, ps::launch_r2c_q3((const float*)d_delta, p->H2, tw, gin, p->batch, st));
+    PS_TIMED(p, POLYSPEC_PH_INPUT_Q2, ps::launch_r2c_q2<false>(p->H2, p->H1, tw, gin, p->batch, st));
+    PS_TIMED(p, POLYSPEC_PH_INPUT_Q1,
+             ps::launch_r2c_q1<false>(p->H1, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, p->box, tw, gin,
+                                      p->batch, st));
   }
   Geom gs = make_geom(p, p->nb, 1);
-  PS_TIMED(p, POLYSPEC_PH_SHELL_P1, ps::launch_c2r_p1<float, false>(p->box, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, p->H1,
-                                            (const cplx<float>*)p->tw32.p, gs, nz, st));
+  PS_TIMED(p, POLYSPEC_PH_SHELL_P1,
+           ps::launch_c2r_p1<float, false>(p->box, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, p->H1,
+                                           (const cplx<float>*)p->tw32.p, gs, nz, st));
   p->absmax_valid = false;
   if (!p->streamed) {   // a streamed plan makes its fields slab by slab in polyspec_contract
     const bool want_max = scaled_contraction(p);
@@ -1412,9 +1419,11 @@ polyspec_status polyspec_shells(polyspec_plan_t p, const void* d_delta) {
 
 // Whether an order-3 plan contracts by contract_j3 (products aligned to shell blocks) or by the
 // pair tiles of contract_tiles.  FP16: always.  FP32 and BF16: plans of one shell block, which are
-// bound by the staging (256^3, 13 shells, FP32: 0.75 against 0.89 ms), where the chunks are
-// whole 256-point stages; the sums are then the same bit for bit.  (Above 32 shells the aligned
-// products multiply j and k first, so the sums of some tuples would differ in the ninth digit.)
+// bound by the staging, where both have the same chunks (not at N = 32), so that the sums are the same
+// bit for bit.  FP32, aligned against pair tiles: 256^3, 6 shells 0.56 against 0.65 ms, 8 to 10
+// 0.73 against 0.68 to 0.70, 13 0.74 against 0.88, 16 0.75 against 1.13; 128^3 x 8, 8 shells 0.66
+// against 0.71.  (Above 32 shells the aligned products multiply j and k first, so the sums of some
+// tuples would differ in the ninth digit.)
 static bool uses_j3(const polyspec_plan_s* p) {
   if (!p->jsched) return false;
   return p->prec == POLYSPEC_SPLIT_FP16 || (p->n_blk == 1 && p->ksteps_j == p->ksteps);
@@ -1644,16 +1653,17 @@ polyspec_status polyspec_backward(polyspec_plan_t p, const double* d_grad_out, v
       gk.x1_0 = slab * p->S1;
     }
     const long long Gk = launch_points(p);
+    float* A = fused ? nullptr : p->A;
+    cplx<float>* H2 = fused ? p->H2 : nullptr;
     if (p->order == 3)
       PS_TIMED(p, POLYSPEC_PH_ADJ_GEMM,
                ps::launch_adjoint_gemm(aprec, p->D, (const uint4*)p->W, (const int*)p->wmask_d.p, p->absmax,
-                                       p->rowmax, p->nb, !p->alias_free, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
-                                       gk, p->batch, st));
+                                       p->rowmax, p->nb, !p->alias_free, Gk, A, H2, tw, gk, p->batch, st));
     else
       PS_TIMED(p, POLYSPEC_PH_ADJ_GEMM,
                ps::launch_adjoint4_gemm(aprec, p->D, (const uint4*)p->W, (const int*)p->wmask_d.p,
-                                        (const int*)p->pmask_d.p, p->absmax, p->rowmax, p->nb, Gk, fused ? nullptr : p->A, fused ? p->H2 : nullptr, tw,
-                                        gk, p->batch, st));
+                                        (const int*)p->pmask_d.p, p->absmax, p->rowmax, p->nb, Gk, A, H2, tw, gk,
+                                        p->batch, st));
     if (!fused) PS_TIMED(p, POLYSPEC_PH_ADJ_Q3, ps::launch_r2c_q3(p->A, p->H2, tw, gk, nz, st));
     PS_TIMED(p, POLYSPEC_PH_ADJ_Q2, ps::launch_r2c_q2<true>(p->H2, H1x, tw, gk, nz, st));
     return POLYSPEC_OK;
@@ -1668,8 +1678,8 @@ polyspec_status polyspec_backward(polyspec_plan_t p, const double* d_grad_out, v
   }
   const size_t box_elems = (size_t)p->B0 * p->B2 * p->B0;
   PS_HIP(p, ps::launch_fill_u32(p->gbox, 0u, (size_t)p->batch * box_elems * 2, st));
-  PS_TIMED(p, POLYSPEC_PH_ADJ_Q1, ps::launch_r2c_q1<true>(H1x, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, p->gbox, tw, gs,
-                                    nz, st));
+  PS_TIMED(p, POLYSPEC_PH_ADJ_Q1, ps::launch_r2c_q1<true>(H1x, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p,
+                                                          p->gbox, tw, gs, nz, st));
   Geom gall = make_geom(p, 0, 0);
   if (p->desc.flags & POLYSPEC_INPUT_HALF_SPECTRUM) {
     // the gradient stays in the input's space: the half spectrum, weighted by how often
@@ -1678,10 +1688,11 @@ polyspec_status polyspec_backward(polyspec_plan_t p, const double* d_grad_out, v
     return POLYSPEC_OK;
   }
   float* grad_x = (float*)d_grad_delta;
-  PS_TIMED(p, POLYSPEC_PH_GRAD_P1, ps::launch_c2r_p1<float, false>(p->gbox, (const int16_t*)p->shell_q.p, (const int*)p->qmax_d.p, H1x,
-                                            tw, gall, p->batch, st));
-  PS_TIMED(p, POLYSPEC_PH_GRAD_P2, ps::launch_c2r_p2<float>(H1x, (const int*)p->qmax_d.p, p->H2, tw, gall, p->batch, st));
-  PS_TIMED(p, POLYSPEC_PH_GRAD_P3, ps::launch_c2r_p3(p->H2, (const int*)p->qmax_d.p, grad_x, nullptr, tw, gall, p->batch, st));
+  const int* qmax = (const int*)p->qmax_d.p;
+  PS_TIMED(p, POLYSPEC_PH_GRAD_P1, ps::launch_c2r_p1<float, false>(p->gbox, (const int16_t*)p->shell_q.p, qmax, H1x, tw,
+                                                                   gall, p->batch, st));
+  PS_TIMED(p, POLYSPEC_PH_GRAD_P2, ps::launch_c2r_p2<float>(H1x, qmax, p->H2, tw, gall, p->batch, st));
+  PS_TIMED(p, POLYSPEC_PH_GRAD_P3, ps::launch_c2r_p3(p->H2, qmax, grad_x, nullptr, tw, gall, p->batch, st));
   return POLYSPEC_OK;
 }
 
