@@ -98,6 +98,15 @@ __device__ __forceinline__ void sym_pin(float (&a)[8]) {
   asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]));
 }
 
+// The sum of a column's two lane halves, in lane half HALF; zero in the other (not multiplied by
+// zero there: the sum may be infinite or NaN).
+template <int HALF>
+__device__ __forceinline__ float sym_half_sum(float x) {
+  const unsigned own = __float_as_uint(x);
+  const auto sw = __builtin_amdgcn_permlane32_swap(HALF == 0 ? own : 0u, HALF == 0 ? 0u : own, false, false);
+  return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+}
+
 // a_m += d_k Y[m] and q_k += d_m Y[m] for the rows of a chain.
 template <int PREC, int KB, bool P, int M, int T>
 __device__ __forceinline__ void sym_add(float (&acc)[kAdjPB][KB][8], float (&q)[2][kAdjPB], const f32x16 (&Y)[kAdjPB],
@@ -215,17 +224,13 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint_sym(const float* __res
           });
         }
       }
-      // a_k += (1/2) sum_m d_m Y_k[m], in the lane half that holds shell k (selected, not
-      // multiplied by 0 in the other half: the sum may be infinite or NaN)
+      // a_k += (1/2) sum_m d_m Y_k[m], in the lane half that holds shell k
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int pb = 0; pb < kAdjPB; ++pb) {
-          const unsigned own = __float_as_uint(q[t][pb]);
-          const auto sw = __builtin_amdgcn_permlane32_swap(own, own, false, false);
-          const float tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
           float& a = acc[pb][kb][(kk + t) % 8];
-          a = fmaf(0.5f, hh == (kk + t) / 8 ? tot : 0.f, a);
+          a = fmaf(0.5f, sym_half_sum<kk / 8>(q[t][pb]), a);
         }
     });
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's part of the next stage is in LDS
@@ -394,11 +399,8 @@ __global__ __launch_bounds__(kAdjThreads, 1) void adjoint4_sym(const float* __re
 #pragma unroll
           for (int pb = 0; pb < kAdjPB; ++pb) {
             al[pb] = fmaf(0.5f * dk[t][pb], q[t][pb], al[pb]);   // this lane half's rows
-            const unsigned own = __float_as_uint(q[t][pb]);
-            const auto sw = __builtin_amdgcn_permlane32_swap(own, own, false, false);
-            const float tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
             float& a = acc[pb][kb][(kk + t) % 8];
-            a = hh == (kk + t) / 8 ? fmaf(0.5f * dl[pb], tot, a) : a;
+            a = fmaf(0.5f * dl[pb], sym_half_sum<kk / 8>(q[t][pb]), a);
           }
       });
     }
